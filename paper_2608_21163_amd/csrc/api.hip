@@ -1378,7 +1378,7 @@ grand_status grand_import_graph(grand_index *h, const void *vecs, const uint32_t
   HCHK(h, hipMemcpyAsync(h->pool.active, active, cap, hipMemcpyDefault, h->stream));
   if ((s = clear_errors(h)) != GRAND_OK) return s;
   if (h->mips) HCHK(h, launch_mips_augment(h->pool.vecs, cap, h->stride, h->p.dim, h->p.mips_norm, h->ds, h->stream));
-  HCHK(h, launch_adj_dists(h->pool, h->stream));
+  HCHK(h, launch_adj_dists(h->pool, h->kind, h->stream));
   HCHK(h, hipMemsetAsync(&h->ds->n_count, 0, sizeof(unsigned long long), h->stream));
   hipLaunchKernelGGL(k_import_check, dim3(4096), dim3(256), 0, h->stream, h->pool, h->ds);
   hipLaunchKernelGGL(k_count_active, dim3(1024), dim3(256), 0, h->stream, h->pool.active, h->p.capacity, h->ds);

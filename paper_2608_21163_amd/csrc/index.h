@@ -259,12 +259,13 @@ hipError_t launch_mips_augment(uint8_t *rows, size_t n, size_t stride, uint32_t 
                                hipStream_t s);
 hipError_t launch_check_finite(const uint8_t *rows, uint32_t n, size_t stride, uint32_t dim, DevScalars *ds,
                                hipStream_t s);
-// Stored list distances apply to Vamana uint8 pools whose list writers are
-// the forward prune and rebuild kernels that maintain them (R <= 64, R a
-// multiple of 4, rows of 64 or 128 bytes, P <= 64, R + P <= 128).
+// Stored list distances apply to Vamana pools whose list writers are the
+// forward prune and rebuild kernels that maintain them: fp32 ones, and uint8
+// ones with R <= 64, R a multiple of 4, rows of 64 or 128 bytes, P <= 64 and
+// R + P <= 128.
 bool adj_dists_apply(int kind, uint32_t R, int nch, uint32_t P);
 // Dist(u, v) for every entry of every list (after a bulk import).
-hipError_t launch_adj_dists(PoolView p, hipStream_t s);
+hipError_t launch_adj_dists(PoolView p, int kind, hipStream_t s);
 hipError_t launch_stage(PoolView p, const uint8_t *rows, const uint32_t *ids, uint32_t n, uint32_t *bidx,
                         hipStream_t s);
 hipError_t launch_mark_batch(const uint32_t *ids, uint32_t n, uint8_t *in_batch, uint32_t *bidx, uint8_t v,

@@ -8,7 +8,7 @@
 // evaluated from LDS.  LDS slots are assigned in ascending id order, so
 // ordering keys by (distance, slot) breaks ties exactly as (distance, id).
 // Rows too long for LDS are read from global memory (L2) instead.
-#include "dispatch.h"
+#include "gram.h"
 
 namespace gr {
 
@@ -366,35 +366,6 @@ __device__ int prune_mfma_u8(const PoolView &P, uint32_t p, int m, uint32_t R, d
     __syncthreads();
   }
   return nsel;
-}
-
-// Greedy selection inside one block of 16 sorted positions, resolved in
-// parallel: kb (lane col) holds the earlier positions that would kill col,
-// vb the live positions.  Each round, an undecided position is rejected if
-// a selected one kills it, and selected if no undecided earlier position
-// can; the lowest undecided position is always decided, so this ends with
-// exactly the set the one-by-one walk selects.
-__device__ __forceinline__ uint32_t block_greedy(uint32_t kb, uint32_t vb, int col, int g) {
-  uint32_t S = 0, U = vb;
-  while (U) {
-    const bool und = ((U >> col) & 1u) != 0;
-    const bool rej = und && (kb & S) != 0u;
-    const bool sel = und && !rej && (kb & U) == 0u;
-    const uint32_t sm = (uint32_t)ballot(sel && g == 0) & 0xFFFFu;
-    const uint32_t rm = (uint32_t)ballot(rej && g == 0) & 0xFFFFu;
-    S |= sm;
-    U &= ~(sm | rm);
-  }
-  return S;
-}
-// The lowest n set bits of m.
-__device__ __forceinline__ uint32_t first_bits(uint32_t m, int n) {
-  uint32_t r = 0;
-  for (int k = 0; k < n && m; k++) {
-    r |= m & (0u - m);
-    m &= m - 1u;
-  }
-  return r;
 }
 
 // The largest integer distance d with coef * d <= D (fp64 product, as in the
@@ -931,12 +902,13 @@ __global__ __launch_bounds__(64) void k_rebuild(RebuildArgs a) {
   }
 }
 
-// C of dirty node u (R <= 64, P <= 64): the kept entries of N_out(u) (minus
-// u and the delete batch) in slot order, then the sources of the P smallest
-// distinct records that are not already kept; written to cl (LDS), and
-// with cdl (LDS, given when the pool stores list distances) D_u of each:
+// C of dirty node u (R <= 64, P <= 64 * NP): the kept entries of N_out(u)
+// (minus u and the delete batch) in slot order, then the sources of the P
+// smallest distinct records that are not already kept; written to cl (LDS),
+// and with cdl (LDS, given when the pool stores list distances) D_u of each:
 // the stored distance of a kept entry, the record's distance of a new one.
 // Returns |C|; nrec is the number of records addressed to u.
+template <int NP>
 __device__ int collect_candidates(const RebuildArgs &a, uint32_t u, uint4 *rowL, uint32_t *cl, uint32_t &nrec,
                                   float *cdl = nullptr) {
   const int ln = lane();
@@ -968,7 +940,7 @@ __device__ int collect_candidates(const RebuildArgs &a, uint32_t u, uint4 *rowL,
   const bool recheck = a.in_batch && (g1 - g0 > 64u || ballot(sin) != 0);
   const bool keep = rok && !rin;
   const uint64_t kmask = ballot(keep);
-  const int kr = popc(kmask);
+  int m = popc(kmask);
   reinterpret_cast<uint32_t *>(rowL)[ln] = keep ? rv : kInvalid;
   if (keep) {
     cl[mbcnt(kmask)] = rv;
@@ -976,31 +948,35 @@ __device__ int collect_candidates(const RebuildArgs &a, uint32_t u, uint4 *rowL,
   }
   __syncthreads();
   // scratch_u: the P smallest distinct (distance, source) records
-  float sd[1] = {finf()};
-  uint32_t si[1] = {kInvalid};
+  float sd[NP];
+  uint32_t si[NP];
+#pragma unroll
+  for (int r = 0; r < NP; r++) {
+    sd[r] = finf();
+    si[r] = kInvalid;
+  }
   for (uint32_t base = g0; base < g1; base += 64) {
     const uint32_t j = base + ln;
     uint32_t sv = j < g1 ? (base == g0 ? s0 : a.gsrc[j]) : kInvalid;
     float dv = j < g1 ? (base == g0 ? d0 : a.gd[j]) : finf();
     if (!kvalid(sv)) { sv = kInvalid; dv = finf(); }
-    wave_merge_new_fast<1>(sd, si, dv, sv, (int)a.P);
+    wave_merge_new_fast<NP>(sd, si, dv, sv, (int)a.P);
   }
-  bool isnew;
-  {
-    const uint32_t sv = si[0];
-    bool ok = kvalid(sv) && sv != u && !(recheck && a.in_batch[sv]);
+#pragma unroll
+  for (int r = 0; r < NP; r++) {
+    const uint32_t sv = si[r];
+    bool isnew = kvalid(sv) && sv != u && !(recheck && a.in_batch[sv]);
 #pragma unroll 4
     for (int t = 0; t < 16; t++) {
       const uint4 r4 = rowL[t];
-      ok = ok & (r4.x != sv) & (r4.y != sv) & (r4.z != sv) & (r4.w != sv);
+      isnew = isnew & (r4.x != sv) & (r4.y != sv) & (r4.z != sv) & (r4.w != sv);
     }
-    isnew = ok;
-  }
-  const uint64_t nmask = ballot(isnew);
-  const int m = kr + popc(nmask);
-  if (isnew) {
-    cl[kr + mbcnt(nmask)] = si[0];
-    if (cdl) cdl[kr + mbcnt(nmask)] = sd[0];
+    const uint64_t nmask = ballot(isnew);
+    if (isnew) {
+      cl[m + mbcnt(nmask)] = sv;
+      if (cdl) cdl[m + mbcnt(nmask)] = sd[r];
+    }
+    m += popc(nmask);
   }
   __syncthreads();
   return m;
@@ -1043,7 +1019,7 @@ __global__ __launch_bounds__(64, 4) void k_rebuild_mr(RebuildArgs a) {
     u_next = a.list[it + gridDim.x < nd_total ? it + gridDim.x : it];
     nodes++;
     uint32_t nrec;
-    const int m = collect_candidates(a, u, rowL, cl, nrec, P.adjd ? cdL : nullptr);
+    const int m = collect_candidates<1>(a, u, rowL, cl, nrec, P.adjd ? cdL : nullptr);
     recs += nrec;
     if (m <= (int)R) {
       if (ln < (int)R) P.adj[(size_t)u * R + ln] = ln < m ? cl[ln] : kInvalid;
@@ -1308,285 +1284,63 @@ __global__ __launch_bounds__(64) void k_rebuild_fast(RebuildArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// fp32 GrANDRobustPrune with one lane per candidate position.  Distances
-// are accumulated in fp64 in dimension order -- the oracle's summation, so
-// every rounded distance is identical -- between each lane's own rows
-// (streamed from the pool in pieces of 16 floats) and up to 16 rows staged in
-// LDS, one slice of kVecSlice floats at a time, which every lane reads at the
-// same address.
-constexpr int kVecSlice = 64;
-
-// st[k][0..kVecSlice) <- floats [d0, d0 + kVecSlice) of pool row ids[k],
-// widened to fp64 once here rather than at every use (k < ns; zeros past
-// the row or for an invalid id).  Lane (k, part) copies 16 floats.
-__device__ __forceinline__ void vec_stage(const PoolView &P, const uint32_t *ids, int ns, int d0, int nfl,
-                                          double (*st)[kVecSlice]) {
-  const int ln = lane(), k = ln >> 2, part = ln & 3;
-  if (k >= ns) return;
-  const uint32_t id = ids[k];
-  const float *row = reinterpret_cast<const float *>(P.vecs + (size_t)(kvalid(id) ? id : 0u) * P.stride);
-  // all four loads issued before any is used: addresses clamped into the
-  // row, the values past it replaced by zeros afterwards
-  uint4 v4[4];
-#pragma unroll
-  for (int h = 0; h < 4; h++) {
-    const int f = d0 + 16 * part + 4 * h;
-    v4[h] = *reinterpret_cast<const uint4 *>(row + (f < nfl ? f : 0));
-  }
-#pragma unroll
-  for (int h = 0; h < 4; h++) {
-    const int f = d0 + 16 * part + 4 * h;
-    const uint4 v = (kvalid(id) && f < nfl) ? v4[h] : make_uint4(0, 0, 0, 0);
-    double2 *dst = reinterpret_cast<double2 *>(&st[k][16 * part + 4 * h]);
-    dst[0] = make_double2((double)__uint_as_float(v.x), (double)__uint_as_float(v.y));
-    dst[1] = make_double2((double)__uint_as_float(v.z), (double)__uint_as_float(v.w));
-  }
-}
-
-// acc[r][k] += the terms of floats [d0, d0 + kVecSlice) between this lane's
-// row own[r] and staged row k, for every register row r with work (act[r],
-// uniform) and every k in kmask (uniform).
-template <int KIND, int NCL, int NS>
-__device__ __forceinline__ void vec_accumulate(const double (*st)[kVecSlice], const float *const (&own)[NCL],
-                                               const bool (&act)[NCL], int d0, int nfl,
-                                               double (&acc)[NCL][NS], uint32_t kmask = ~0u) {
-  for (int pc = 0; pc < kVecSlice && d0 + pc < nfl; pc += 16) {
-#pragma unroll
-    for (int r = 0; r < NCL; r++) {
-      if (!act[r]) continue;
-      float xv[16];
-      // rows hold nfl floats, a multiple of 4; all four loads are issued
-      // before any is used (addresses clamped into the row, the values past
-      // it replaced by zeros afterwards)
-      uint4 v4[4];
-#pragma unroll
-      for (int h = 0; h < 4; h++) {
-        const int f = d0 + pc + 4 * h;
-        v4[h] = *reinterpret_cast<const uint4 *>(own[r] + (f < nfl ? f : 0));
-      }
-#pragma unroll
-      for (int h = 0; h < 4; h++) {
-        const int f = d0 + pc + 4 * h;
-        const uint4 v = f < nfl ? v4[h] : make_uint4(0, 0, 0, 0);
-        xv[4 * h + 0] = __uint_as_float(v.x);
-        xv[4 * h + 1] = __uint_as_float(v.y);
-        xv[4 * h + 2] = __uint_as_float(v.z);
-        xv[4 * h + 3] = __uint_as_float(v.w);
-      }
-#pragma unroll
-      for (int k = 0; k < NS; k++) {
-        if (!((kmask >> k) & 1u)) continue;  // staged row k is not needed
-#pragma unroll
-        for (int t = 0; t < 16; t++) {
-          if (KIND == kF32IP) {
-            acc[r][k] = __builtin_fma((double)xv[t], st[k][pc + t], acc[r][k]);
-          } else {
-            const double df = st[k][pc + t] - (double)xv[t];
-            acc[r][k] = __builtin_fma(df, df, acc[r][k]);
-          }
-        }
-      }
-    }
-  }
-}
-
-// GrANDRobustPrune over m candidates sorted by (D_p, id) (spos/dpos in LDS,
-// positions e = r*64 + lane, at most 64*NCL).  Positions are taken in blocks
-// of NPB pivots: the block's rows are staged and the distances from them to
-// every still-live position from the block on are computed, those positions
-// packed onto the lanes (a block rarely leaves more than 64 of them, so the
-// fp64 work follows the live positions, not the register rows); the block's
-// own selections come from the parallel fixpoint, and later positions that a
-// selected pivot kills (coef * Dist <= D, in fp64 on the rounded distance)
-// are dropped.  Pivots already dead take no distance work.  The selections go to oid/od (LDS) in order; returns their
-// number.
-template <int KIND, int NCL, int NPB>
-__device__ int prune_vec(const PoolView &P, uint32_t p, int m, uint32_t R, double coef, const uint32_t *spos,
-                         const float *dpos, double (*st)[kVecSlice], uint32_t *oid, float *od, uint32_t &evals) {
-  static_assert(NPB <= 16 && 64 % NPB == 0, "pivot blocks inside one register row");
-  __shared__ uint32_t lpos[64 * NCL];  // live positions of the block, packed
-  __shared__ uint32_t kmL[64 * NCL];   // kill masks by position
-  const int ln = lane(), g = ln >> 4, col = ln & 15;
-  const int nfl = P.nch * 4;
-  uint64_t vm[NCL];
-#pragma unroll
-  for (int r = 0; r < NCL; r++) vm[r] = ballot(r * 64 + ln < m);
-  int nsel = 0;
-  const int nb = (m + NPB - 1) / NPB;
-  for (int b = 0; b < nb; b++) {
-    const int p0 = b * NPB;
-    uint64_t vr = 0;
-#pragma unroll
-    for (int r = 0; r < NCL; r++)
-      if (r == (p0 >> 6)) vr = vm[r];
-    const uint32_t vb = (uint32_t)(vr >> (p0 & 63)) & ((1u << NPB) - 1u);
-    if (!vb) continue;
-    // live positions >= p0, in order, packed onto the lanes
-    int nl = 0;
-#pragma unroll
-    for (int r = 0; r < NCL; r++) {
-      const int e = r * 64 + ln;
-      const bool lv = e >= p0 && ((vm[r] >> ln) & 1ull);
-      const uint64_t bm = ballot(lv);
-      if (lv) lpos[nl + mbcnt(bm)] = (uint32_t)e;
-      nl += popc(bm);
-    }
-    __syncthreads();
-    bool act[NCL];
-    const float *own[NCL];
-    int ep[NCL];
-#pragma unroll
-    for (int r = 0; r < NCL; r++) {
-      act[r] = r * 64 < nl;
-      const int c = r * 64 + ln;
-      ep[r] = act[r] && c < nl ? (int)lpos[c] : -1;
-      own[r] = reinterpret_cast<const float *>(P.vecs + (size_t)(ep[r] >= 0 ? spos[ep[r]] : p) * P.stride);
-    }
-    double acc[NCL][NPB];
-#pragma unroll
-    for (int r = 0; r < NCL; r++)
-#pragma unroll
-      for (int k = 0; k < NPB; k++) acc[r][k] = 0.0;
-    for (int d0 = 0; d0 < nfl; d0 += kVecSlice) {
-      __syncthreads();
-      vec_stage(P, spos + p0, min(NPB, m - p0), d0, nfl, st);
-      __syncthreads();
-      vec_accumulate<KIND, NCL, NPB>(st, own, act, d0, nfl, acc, vb);
-    }
-    // kill masks of the packed positions, scattered back by position
-#pragma unroll
-    for (int r = 0; r < NCL; r++) {
-      const int e = ep[r];
-      if (e < 0) continue;
-      const double De = (double)dpos[e];
-      uint32_t km = 0;
-#pragma unroll
-      for (int k = 0; k < NPB; k++) {
-        const bool kill = ((vb >> k) & 1u) && e > p0 + k && coef * (double)finalize<KIND>(acc[r][k]) <= De;
-        km |= kill ? (1u << k) : 0u;
-      }
-      kmL[e] = km;
-    }
-    evals += (uint32_t)(__popc(vb) * nl);
-    __syncthreads();
-    // km[r]: pivots of the block that kill this lane's position
-    uint32_t km[NCL];
-#pragma unroll
-    for (int r = 0; r < NCL; r++) {
-      const int e = r * 64 + ln;
-      km[r] = e >= p0 && ((vm[r] >> ln) & 1ull) ? kmL[e] : 0u;
-    }
-    // the block's own positions: lanes (p0 & 63) + col of register row p0 >> 6
-    uint32_t kbr = 0;
-#pragma unroll
-    for (int r = 0; r < NCL; r++)
-      if (r == (p0 >> 6)) kbr = km[r];
-    const uint32_t kb = (uint32_t)__shfl((int)kbr, ((p0 & 63) + col) & 63, 64) & ((1u << col) - 1u);
-    uint32_t S = block_greedy(kb, vb, col, g);
-    int ns = __popc(S);
-    const int room = (int)R - nsel;
-    bool done = false;
-    if (ns >= room) {
-      S = first_bits(S, room);
-      ns = room;
-      done = true;
-    }
-    if (g == 0 && ((S >> col) & 1u)) {
-      const int pos = nsel + __popc(S & ((1u << col) - 1u));
-      oid[pos] = spos[p0 + col];
-      od[pos] = dpos[p0 + col];
-    }
-    nsel += ns;
-    if (done) break;
-#pragma unroll
-    for (int r = 0; r < NCL; r++) {
-      const int e = r * 64 + ln;
-      vm[r] &= ~ballot(e >= p0 + NPB && (km[r] & S) != 0u);
-    }
-    __syncthreads();
-  }
-  __syncthreads();
-  return nsel;
-}
-
-// Rebuild of queued dirty nodes for fp32 rows with R <= 64 and R + P <= 128:
-// C as in k_rebuild_mr; D_u of every candidate from u's staged row, a
-// 64-bit-key sort, then prune_vec.
-template <int KIND>
-__global__ __launch_bounds__(64) void k_rebuild_vec(RebuildArgs a) {
-  constexpr int NC = 2;
+// fp32 rebuild of queued dirty nodes (R <= 64, P <= 64 * NP), one wave per
+// node, persistent over twice the resident workgroups: C and its distances as
+// in k_rebuild_mr (stored list distances, records), a 64-bit-key sort, then
+// prune_gram.
+template <int NP>
+__global__ __launch_bounds__(64, 3) void k_rebuild_gram(RebuildArgs a) {
+  constexpr int NC = NP == 1 ? 2 : 4;  // 64 + 64 * NP candidates at most, in a power of two of rows
   __shared__ uint4 rowL[16];
   __shared__ uint32_t cl[64 * NC];
-  __shared__ uint32_t spos[64 * NC];
-  __shared__ float dpos[64 * NC];
-  __shared__ double st[16][kVecSlice];
+  __shared__ __align__(16) float cdL[64 * NC];
   __shared__ uint32_t oid[64];
   __shared__ float od[64];
-  __shared__ uint32_t uid[1];
   const int ln = lane();
   const PoolView &P = a.pool;
   const uint32_t R = P.R;
-  const int nfl = P.nch * 4;
   const uint32_t nd_total = *a.list_n;
-  uint32_t evals = 0, prunes = 0, nodes = 0, recs = 0, cand = 0;
+  uint32_t ntile = 0, prunes = 0, nodes = 0, recs = 0, cand = 0;
   for (uint32_t it = blockIdx.x; it < nd_total; it += gridDim.x) {
     const uint32_t u = a.list[it];
     nodes++;
     uint32_t nrec;
-    const int m = collect_candidates(a, u, rowL, cl, nrec);
+    const int m = collect_candidates<NP>(a, u, rowL, cl, nrec, cdL);
     recs += nrec;
-    if (m <= (int)R) {
-      if (ln < (int)R) P.adj[(size_t)u * R + ln] = ln < m ? cl[ln] : kInvalid;
-      if (ln == 0) P.deg[u] = (uint32_t)m;
-      __syncthreads();
-      continue;
-    }
-    // D_u of every candidate (list order)
-    {
-      const float *own[NC];
-      bool act[NC];
-#pragma unroll
-      for (int r = 0; r < NC; r++) {
-        const int e = r * 64 + ln;
-        own[r] = reinterpret_cast<const float *>(P.vecs + (size_t)(e < m ? cl[e] : u) * P.stride);
-        act[r] = r * 64 < m;
-      }
-      double du[NC][1];
-#pragma unroll
-      for (int r = 0; r < NC; r++) du[r][0] = 0.0;
-      if (ln == 0) uid[0] = u;
-      for (int d0 = 0; d0 < nfl; d0 += kVecSlice) {
-        __syncthreads();
-        vec_stage(P, uid, 1, d0, nfl, st);
-        __syncthreads();
-        vec_accumulate<KIND, NC, 1>(st, own, act, d0, nfl, du);
-      }
-      evals += (uint32_t)m;
+    int n = m;
+    const uint32_t *ids = cl;
+    const float *ds = cdL;
+    if (m > (int)R) {
       uint64_t key[NC];
 #pragma unroll
       for (int r = 0; r < NC; r++) {
         const int e = r * 64 + ln;
-        key[r] = e < m ? key64(finalize<KIND>(du[r][0]), cl[e]) : ~0ull;
+        key[r] = e < m ? key64(cdL[e], cl[e]) : ~0ull;
       }
       __syncthreads();
       wave_sort64<NC>(key);
 #pragma unroll
       for (int r = 0; r < NC; r++) {
-        spos[r * 64 + ln] = (uint32_t)key[r];
-        dpos[r * 64 + ln] = unsortable((uint32_t)(key[r] >> 32));
+        cl[r * 64 + ln] = (uint32_t)key[r];
+        cdL[r * 64 + ln] = unsortable((uint32_t)(key[r] >> 32));
       }
       __syncthreads();
+      n = prune_gram<NC>(P, u, m, R, a.coef, cl, cdL, oid, od, ntile);
+      ids = oid;
+      ds = od;
+      prunes++;
+      cand += (uint32_t)m + 1;
     }
-    const int nsel = prune_vec<KIND, NC, 16>(P, u, m, R, a.coef, spos, dpos, st, oid, od, evals);
-    if (ln < (int)R) P.adj[(size_t)u * R + ln] = ln < nsel ? oid[ln] : kInvalid;
-    if (ln == 0) P.deg[u] = (uint32_t)nsel;
-    prunes++;
-    cand += (uint32_t)m + 1;
+    if (ln < (int)R) {
+      P.adj[(size_t)u * R + ln] = ln < n ? ids[ln] : kInvalid;
+      P.adjd[(size_t)u * R + ln] = ln < n ? ds[ln] : 0.0f;
+    }
+    if (ln == 0) P.deg[u] = (uint32_t)n;
     __syncthreads();
   }
   if (ln == 0) {
     stat_add(a.ds, kStRbPrunes, (unsigned long long)prunes);
-    stat_add(a.ds, kStRbEvals, (unsigned long long)evals);
+    stat_add(a.ds, kStRbEvals, 256ull * ntile);
     stat_add(a.ds, kStRbCand, (unsigned long long)cand);
     if (a.count_nodes) {
       stat_add(a.ds, kStDirty, (unsigned long long)nodes);
@@ -1596,13 +1350,11 @@ __global__ __launch_bounds__(64) void k_rebuild_vec(RebuildArgs a) {
 }
 
 // Forward GrANDRobustPrune of new fp32 points: V_i with the search's D, a
-// 64-bit-key sort, then prune_vec (blocks of 8 pivots for 256 candidates).
-template <int KIND, int NR>
-__global__ __launch_bounds__(64) void k_fwd_prune_vec(FwdPruneArgs a) {
-  constexpr int NPB = NR >= 4 ? 8 : 16;
-  __shared__ uint32_t spos[64 * NR];
-  __shared__ float dpos[64 * NR];
-  __shared__ double st[16][kVecSlice];
+// 64-bit-key sort, then prune_gram.
+template <int NR>
+__global__ __launch_bounds__(64, 3) void k_fwd_prune_gram(FwdPruneArgs a) {
+  __shared__ uint32_t spos[64 * (NR < 2 ? 2 : NR)];
+  __shared__ __align__(16) float dpos[64 * (NR < 2 ? 2 : NR)];
   __shared__ uint32_t oid[64];
   __shared__ float od[64];
   const int ln = lane();
@@ -1630,20 +1382,22 @@ __global__ __launch_bounds__(64) void k_fwd_prune_vec(FwdPruneArgs a) {
     dpos[r * 64 + ln] = unsortable((uint32_t)(key[r] >> 32));
   }
   __syncthreads();
-  uint32_t evals = 0;
-  const int nsel = prune_vec<KIND, NR, NPB>(P, p, m, R, a.coef, spos, dpos, st, oid, od, evals);
+  uint32_t ntile = 0;
+  const int nsel = prune_gram<NR>(P, p, m, R, a.coef, spos, dpos, oid, od, ntile);
   if (ln < (int)R) {
     const bool in = ln < nsel;
     const uint32_t sid = in ? oid[ln] : kInvalid;
+    const float sd = in ? od[ln] : 0.0f;
     P.adj[(size_t)p * R + ln] = sid;
+    P.adjd[(size_t)p * R + ln] = sd;
     a.rec_t[(size_t)i * R + ln] = sid;
     a.rec_s[(size_t)i * R + ln] = p;
-    a.rec_d[(size_t)i * R + ln] = in ? od[ln] : 0.0f;
+    a.rec_d[(size_t)i * R + ln] = sd;
   }
   if (ln == 0) {
     P.deg[p] = (uint32_t)nsel;
     stat_add(a.ds, kStFwdPrunes, 1ull);
-    stat_add(a.ds, kStFwdEvals, (unsigned long long)evals);
+    stat_add(a.ds, kStFwdEvals, 256ull * ntile);
     stat_add(a.ds, kStRecords, (unsigned long long)nsel);
   }
 }
@@ -1665,24 +1419,19 @@ hipError_t launch_fwd_prune(int kind, int vc, uint32_t max_iters, const FwdPrune
       return hipGetLastError();
     });
   }
-  // fp32 rows longer than 32 floats: one lane per live candidate (the
-  // per-pivot walk of the general kernel costs more there; measured at
-  // d = 96 and 960)
-  if (kind != kU8L2 && a.pool.R <= 64 && a.pool.nch > 8) {
+  if (kind == kF32L2) {
     GR_DISPATCH_N(max_iters, {
-      if (kind == kF32L2) hipLaunchKernelGGL((k_fwd_prune_vec<kF32L2, NR>), dim3(a.n), dim3(64), 0, st, a);
-      else hipLaunchKernelGGL((k_fwd_prune_vec<kF32IP, NR>), dim3(a.n), dim3(64), 0, st, a);
+      hipLaunchKernelGGL((k_fwd_prune_gram<NR>), dim3(a.n), dim3(64), 0, st, a);
       return hipGetLastError();
     });
   }
-  GR_DISPATCH_KV(kind, vc, GR_DISPATCH_N(max_iters, {
+  if (kind != kU8L2) return hipErrorInvalidValue;  // Vamana lists are pruned by L2 distances
+  GR_DISPATCH_VC_U8(vc, GR_DISPATCH_N(max_iters, {
     const size_t lds = staged_bytes(a.pool.stride, 64 * NR);
     const size_t mlds = mfma_lds_bytes(a.pool.stride, 64 * NR);
-    if constexpr (KIND == kU8L2) {
-      if (mfma_ok(kind, a.pool) && mlds <= kMaxStagedLds) {
-        hipLaunchKernelGGL((k_fwd_prune<KIND, LPV, CPL, NR, kMfma>), dim3(a.n), dim3(64), mlds, st, a);
-        return hipGetLastError();
-      }
+    if (mfma_ok(kind, a.pool) && mlds <= kMaxStagedLds) {
+      hipLaunchKernelGGL((k_fwd_prune<KIND, LPV, CPL, NR, kMfma>), dim3(a.n), dim3(64), mlds, st, a);
+      return hipGetLastError();
     }
     if (lds <= kMaxStagedLds) {
       hipLaunchKernelGGL((k_fwd_prune<KIND, LPV, CPL, NR, kStaged>), dim3(a.n), dim3(64), lds, st, a);
@@ -1699,14 +1448,7 @@ template <int KIND, int LPV, int CPL, int NP, int NC>
 static void launch_rebuild_t(const RebuildArgs &a, uint32_t grid, hipStream_t st) {
   const size_t lds = staged_bytes(a.pool.stride, 64 * NC);
   const size_t mlds = mfma_lds_bytes(a.pool.stride, 64 * NC);
-  if constexpr (KIND != kU8L2 && NC == 2 && NP == 1) {
-    if (a.pool.R <= 64) {
-      static const uint32_t res = resident_blocks((const void *)k_rebuild_vec<KIND>);
-      hipLaunchKernelGGL((k_rebuild_vec<KIND>), dim3(clamp_resident(grid, 2 * res)), dim3(64), 0, st, a);
-      return;
-    }
-  }
-  if constexpr (KIND == kU8L2 && NC == 2 && NP == 1) {
+  if constexpr (NC == 2 && NP == 1) {
     // persistent waves, twice the resident workgroups: the second half
     // starts as the first ones finish, which evens out the work per wave
     if (a.pool.R <= 64 && a.pool.nch == 8) {
@@ -1720,11 +1462,9 @@ static void launch_rebuild_t(const RebuildArgs &a, uint32_t grid, hipStream_t st
       return;
     }
   }
-  if constexpr (KIND == kU8L2) {
-    if (mfma_ok(KIND, a.pool) && mlds <= kMaxStagedLds) {
-      hipLaunchKernelGGL((k_rebuild<KIND, LPV, CPL, NP, NC, kMfma>), dim3(grid), dim3(64), mlds, st, a);
-      return;
-    }
+  if (mfma_ok(KIND, a.pool) && mlds <= kMaxStagedLds) {
+    hipLaunchKernelGGL((k_rebuild<KIND, LPV, CPL, NP, NC, kMfma>), dim3(grid), dim3(64), mlds, st, a);
+    return;
   }
   if (lds <= kMaxStagedLds) {
     hipLaunchKernelGGL((k_rebuild<KIND, LPV, CPL, NP, NC, kStaged>), dim3(grid), dim3(64), lds, st, a);
@@ -1734,11 +1474,14 @@ static void launch_rebuild_t(const RebuildArgs &a, uint32_t grid, hipStream_t st
 }
 
 bool adj_dists_apply(int kind, uint32_t R, int nch, uint32_t P) {
+  if (kind == kF32L2) return true;
   return kind == kU8L2 && R <= 64 && R % 4 == 0 && (nch == 8 || nch == 4) && P <= 64 && R + P <= 128;
 }
 
-// One wave per row, lane s for list entry s: the exact uint8 squared
-// distance of u and its s-th neighbour (0 for an empty slot).
+// One wave per row, lane s for list entry s: the squared distance of u and
+// its s-th neighbour (0 for an empty slot), exact for uint8 rows, summed in
+// fp64 in dimension order and rounded once for fp32 rows.
+template <int KIND>
 __global__ void k_adj_dists(PoolView P) {
   const int ln = threadIdx.x & 63;
   const uint32_t w0 = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
@@ -1749,25 +1492,30 @@ __global__ void k_adj_dists(PoolView P) {
     if (kvalid(v) && v < P.cap) {
       const uint4 *x = reinterpret_cast<const uint4 *>(P.vecs + (size_t)u * P.stride);
       const uint4 *y = reinterpret_cast<const uint4 *>(P.vecs + (size_t)v * P.stride);
-      uint32_t acc = 0;
+      typename Acc<KIND>::T acc = 0;
       for (int c = 0; c < P.nch; c++) {
         const uint4 a = x[c], b = y[c];
-        acc = udot4(a.x, a.x, acc);
-        acc = udot4(a.y, a.y, acc);
-        acc = udot4(a.z, a.z, acc);
-        acc = udot4(a.w, a.w, acc);
-        acc = u8l2_4(a, b, acc);  // + |b|^2 - 2 a.b
+        if constexpr (KIND == kU8L2) {
+          acc = udot4(a.x, a.x, acc);
+          acc = udot4(a.y, a.y, acc);
+          acc = udot4(a.z, a.z, acc);
+          acc = udot4(a.w, a.w, acc);
+          acc = u8l2_4(a, b, acc);  // + |b|^2 - 2 a.b
+        } else {
+          acc = l2_4(a, b, acc);
+        }
       }
-      d = canon0((float)acc);
+      d = finalize<KIND>(acc);
     }
     P.adjd[(size_t)u * P.R + ln] = d;
   }
 }
-hipError_t launch_adj_dists(PoolView p, hipStream_t s) {
+hipError_t launch_adj_dists(PoolView p, int kind, hipStream_t s) {
   if (!p.adjd || p.cap == 0) return hipSuccess;
   size_t g = ((size_t)p.cap * 64 + 255) / 256;
   if (g > 16384) g = 16384;
-  hipLaunchKernelGGL(k_adj_dists, dim3((uint32_t)g), dim3(256), 0, s, p);
+  if (kind == kU8L2) hipLaunchKernelGGL(k_adj_dists<kU8L2>, dim3((uint32_t)g), dim3(256), 0, s, p);
+  else hipLaunchKernelGGL(k_adj_dists<kF32L2>, dim3((uint32_t)g), dim3(256), 0, s, p);
   return hipGetLastError();
 }
 
@@ -1791,7 +1539,15 @@ hipError_t launch_rebuild(int kind, int vc, uint32_t R, uint32_t P, const Rebuil
     a.list_n = a0.queue_n;
     a.count_nodes = 0;
   }
-  GR_DISPATCH_KV(kind, vc, {
+  if (kind == kF32L2) {
+    static const uint32_t r1 = resident_blocks((const void *)k_rebuild_gram<1>);
+    static const uint32_t r2 = resident_blocks((const void *)k_rebuild_gram<2>);
+    if (P <= 64) hipLaunchKernelGGL(k_rebuild_gram<1>, dim3(clamp_resident(grid, 2 * r1)), dim3(64), 0, st, a);
+    else hipLaunchKernelGGL(k_rebuild_gram<2>, dim3(clamp_resident(grid, 2 * r2)), dim3(64), 0, st, a);
+    return hipGetLastError();
+  }
+  if (kind != kU8L2) return hipErrorInvalidValue;
+  GR_DISPATCH_VC_U8(vc, {
     if (P <= 64 && R + P <= 128) {
       launch_rebuild_t<KIND, LPV, CPL, 1, 2>(a, grid, st);
     } else if (P <= 64) {
