@@ -51,6 +51,14 @@ uint8_t *scratch_of(int dev, hipError_t *err) {
 }
 }  // namespace
 
+// Device buffer for packed rows copied from host memory (see copy_rows);
+// at most kRowStageBytes (or one row), kept for the next call.
+constexpr size_t kRowStageBytes = (size_t)16 << 20;
+struct RowStage {
+  uint8_t *buf = nullptr;
+  size_t bytes = 0;
+};
+
 struct grand_index {
   grand_params p{};
   hipStream_t stream = nullptr;
@@ -92,6 +100,7 @@ struct grand_index {
   size_t rcap = 0;
   uint32_t *rec_t = nullptr, *rec_s = nullptr, *gsrc = nullptr;
   float *rec_d = nullptr, *gd = nullptr;
+  RowStage rows;  // packed rows from host memory on their way into padded ones
   // query buffers
   uint32_t qcap = 0, qk = 0;
   uint8_t *q_vecs = nullptr;
@@ -299,9 +308,67 @@ grand_status ensure_query(grand_index *h, uint32_t nq, uint32_t k) {
   return GRAND_OK;
 }
 
+// Whether a copy from p is a copy on the GPU (else p is host memory).
+bool on_device(const void *p) {
+  hipPointerAttribute_t a{};
+  if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return a.type == hipMemoryTypeDevice;
+}
+
+// Copies n packed rows of row_bytes (host or device memory) to rows of
+// `stride` bytes.  A 2-D copy from host memory moves one row at a time (about
+// 9 us each: 8.9 ms for 1,000 queries of 96 floats), so rows that need no
+// padding go as one block, and padded ones from host memory as blocks through
+// `st`, spread to their places on the device (1,000 rows: 20 to 40 us).  With
+// st null nothing is allocated: `spare` bytes at `tmp` stand in for it, and
+// rows that don't fit there take the 2-D copy.
+hipError_t copy_rows(uint8_t *dst, size_t stride, const void *src, size_t row_bytes, size_t n, RowStage *st,
+                     uint8_t *tmp, size_t spare, hipStream_t s) {
+  if (n == 0) return hipSuccess;
+  if (stride == row_bytes) return hipMemcpyAsync(dst, src, n * row_bytes, hipMemcpyDefault, s);
+  size_t step = 0;
+  if (!on_device(src)) {
+    if (st) {
+      const size_t want = std::max(row_bytes, std::min(n * row_bytes, kRowStageBytes));
+      if (st->bytes < want) {
+        if (st->buf) {
+          hipError_t e = hipStreamSynchronize(s);
+          if (e != hipSuccess) return e;
+          (void)hipFree(st->buf);
+          st->buf = nullptr;
+          st->bytes = 0;
+        }
+        if (hipMalloc((void **)&st->buf, want) == hipSuccess) {
+          st->bytes = want;
+        } else {
+          (void)hipGetLastError();  // no room: row by row below
+          st->buf = nullptr;
+        }
+      }
+      tmp = st->buf;
+      spare = st->bytes;
+    }
+    step = spare / row_bytes;
+    if (!st && step < n) step = 0;
+  }
+  if (step == 0) return hipMemcpy2DAsync(dst, stride, src, row_bytes, row_bytes, n, hipMemcpyDefault, s);
+  for (size_t r = 0; r < n; r += step) {
+    const size_t m = std::min(step, n - r);
+    hipError_t e = hipMemcpyAsync(tmp, static_cast<const uint8_t *>(src) + r * row_bytes, m * row_bytes,
+                                  hipMemcpyDefault, s);
+    if (e == hipSuccess)
+      e = hipMemcpy2DAsync(dst + r * stride, stride, tmp, row_bytes, row_bytes, m, hipMemcpyDeviceToDevice, s);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 // Copies n packed rows (host or device) into a padded staging buffer.
-grand_status stage_rows(grand_index *h, uint8_t *dst, const void *src, uint32_t n) {
-  HCHK(h, hipMemcpy2DAsync(dst, h->stride, src, h->row_bytes, h->row_bytes, n, hipMemcpyDefault, h->stream));
+grand_status stage_rows(grand_index *h, uint8_t *dst, const void *src, size_t n) {
+  HCHK(h, copy_rows(dst, h->stride, src, h->row_bytes, n, &h->rows, nullptr, 0, h->stream));
   return GRAND_OK;
 }
 
@@ -663,7 +730,7 @@ void release(grand_index *h) {
   dfree(h->grp.pt); dfree(h->grp.ps); dfree(h->grp.pd); dfree(h->grp.mat); dfree(h->grp.mato); dfree(h->grp.tmp);
   dfree(h->grp.dpad); dfree(h->grp.dcnt);
   dfree(h->q_vecs); dfree(h->q_ids); dfree(h->q_d);
-  dfree(h->vis);
+  dfree(h->vis); dfree(h->rows.buf);
   for (auto &t : h->pending) {
     if (std::get<1>(t)) (void)hipEventDestroy(std::get<1>(t));
     if (std::get<2>(t)) (void)hipEventDestroy(std::get<2>(t));
@@ -1098,7 +1165,8 @@ grand_status grand_search_static(grand_index *h, const void *queries, uint32_t n
   float *q_d = reinterpret_cast<float *>(h->static_scratch + qb + rb);
   // the array keeps the previous call's contents: zero the rows' padding
   if (h->stride != h->row_bytes) HCHK(h, launch_fill_u32(reinterpret_cast<uint32_t *>(q_vecs), 0u, qb / 4, h->stream));
-  if ((s = stage_rows(h, q_vecs, queries, nq)) != GRAND_OK) return s;
+  HCHK(h, copy_rows(q_vecs, h->stride, queries, h->row_bytes, nq, nullptr, h->static_scratch + qb + 2 * rb,
+                    kStaticScratchBytes - qb - 2 * rb, h->stream));
   if (h->p.dtype == GRAND_F32) {
     if ((s = clear_errors(h)) != GRAND_OK) return s;
     HCHK(h, launch_check_finite(q_vecs, nq, h->stride, h->p.dim, h->ds, h->stream));
@@ -1182,6 +1250,7 @@ struct grand_reader {
   uint8_t *q_vecs = nullptr;
   uint32_t *q_ids = nullptr;
   float *q_d = nullptr;
+  RowStage rows;
   uint32_t qcap = 0, qk = 0;
   DevScalars *ds = nullptr;  // the reader's own error flags and counters
   DevScalars *hs = nullptr;  // pinned host mirror
@@ -1190,7 +1259,7 @@ struct grand_reader {
 
 namespace {
 void reader_release(grand_reader *r) {
-  dfree(r->q_vecs); dfree(r->q_ids); dfree(r->q_d); dfree(r->ds);
+  dfree(r->q_vecs); dfree(r->q_ids); dfree(r->q_d); dfree(r->ds); dfree(r->rows.buf);
   if (r->hs) (void)hipHostFree(r->hs);
   if (r->own_stream && r->stream) (void)hipStreamDestroy(r->stream);
 }
@@ -1266,7 +1335,7 @@ grand_status grand_reader_search(grand_reader *r, const void *queries, uint32_t 
     r->qcap = nc;
     r->qk = kc;
   }
-  RCHK(r, hipMemcpy2DAsync(r->q_vecs, h->stride, queries, h->row_bytes, h->row_bytes, nq, hipMemcpyDefault, r->stream));
+  RCHK(r, copy_rows(r->q_vecs, h->stride, queries, h->row_bytes, nq, &r->rows, nullptr, 0, r->stream));
   if (h->p.dtype == GRAND_F32) {
     RCHK(r, launch_fill_u32(&r->ds->err_code, 0u, 2, r->stream));
     RCHK(r, launch_check_finite(r->q_vecs, nq, h->stride, h->p.dim, r->ds, r->stream));
@@ -1371,8 +1440,7 @@ grand_status grand_import_graph(grand_index *h, const void *vecs, const uint32_t
   if (!vecs || !adj || !deg || !active) return fail(h, GRAND_E_ARG, "null argument");
   HCHK(h, hipSetDevice(h->p.device));
   const size_t cap = h->p.capacity;
-  HCHK(h, hipMemcpy2DAsync(h->pool.vecs, h->stride, vecs, h->row_bytes, h->row_bytes, cap, hipMemcpyDefault,
-                           h->stream));
+  if ((s = stage_rows(h, h->pool.vecs, vecs, cap)) != GRAND_OK) return s;
   HCHK(h, hipMemcpyAsync(h->pool.adj, adj, cap * h->p.R * 4, hipMemcpyDefault, h->stream));
   HCHK(h, hipMemcpyAsync(h->pool.deg, deg, cap * 4, hipMemcpyDefault, h->stream));
   HCHK(h, hipMemcpyAsync(h->pool.active, active, cap, hipMemcpyDefault, h->stream));
