@@ -64,7 +64,9 @@ struct grand_index {
   hipStream_t stream = nullptr;
   uint8_t *static_scratch = nullptr;  // this device's address of `scratch`
   int kind = 0, vc = 0;
-  size_t esize = 0, row_bytes = 0, stride = 0;  // caller row bytes; stored row bytes (16-byte multiple)
+  size_t esize = 0, row_bytes = 0;  // bytes of an element and of a caller's row
+  size_t stride = 0;                // bytes of a pool row
+  size_t q_stride = 0;              // bytes of a staged query row
   uint32_t sdim = 0;   // stored elements per row: dim, or dim + 1 with GRAND_MIPS
   bool mips = false;
   int nch = 0;
@@ -297,12 +299,12 @@ grand_status ensure_query(grand_index *h, uint32_t nq, uint32_t k) {
   const uint32_t nc = std::max(nq, h->qcap), kc = std::max(k, h->qk);
   dfree(h->q_vecs); dfree(h->q_ids); dfree(h->q_d);
   h->qcap = h->qk = 0;
-  if (dalloc(&h->q_vecs, (size_t)nc * h->stride) || dalloc(&h->q_ids, (size_t)nc * kc) ||
+  if (dalloc(&h->q_vecs, (size_t)nc * h->q_stride) || dalloc(&h->q_ids, (size_t)nc * kc) ||
       dalloc(&h->q_d, (size_t)nc * kc)) {
     (void)hipGetLastError();
     return fail(h, GRAND_E_OOM, "device allocation of query buffers failed");
   }
-  HCHK(h, hipMemset(h->q_vecs, 0, (size_t)nc * h->stride));
+  HCHK(h, hipMemset(h->q_vecs, 0, (size_t)nc * h->q_stride));
   h->qcap = nc;
   h->qk = kc;
   return GRAND_OK;
@@ -367,8 +369,8 @@ hipError_t copy_rows(uint8_t *dst, size_t stride, const void *src, size_t row_by
 }
 
 // Copies n packed rows (host or device) into a padded staging buffer.
-grand_status stage_rows(grand_index *h, uint8_t *dst, const void *src, size_t n) {
-  HCHK(h, copy_rows(dst, h->stride, src, h->row_bytes, n, &h->rows, nullptr, 0, h->stream));
+grand_status stage_rows(grand_index *h, uint8_t *dst, size_t stride, const void *src, size_t n) {
+  HCHK(h, copy_rows(dst, stride, src, h->row_bytes, n, &h->rows, nullptr, 0, h->stream));
   return GRAND_OK;
 }
 
@@ -402,7 +404,7 @@ grand_status run_rebuild(grand_index *h, size_t nrec, const uint8_t *in_batch) {
   a.P = h->p.P;
   a.coef = h->coef;
   a.ds = h->ds;
-  HCHK(h, launch_rebuild(h->kind, h->vc, h->p.R, h->p.P, a, persistent_grid(nrec), h->stream));
+  HCHK(h, launch_rebuild(h->kind, h->p.R, h->p.P, a, persistent_grid(nrec), h->stream));
   return GRAND_OK;
 }
 
@@ -495,7 +497,7 @@ grand_status vamana_insert(grand_index *h, uint32_t n, uint64_t n0) {
     f.rec_s = h->rec_s;
     f.rec_d = h->rec_d;
     f.ds = h->ds;
-    HCHK(h, launch_fwd_prune(h->kind, h->vc, h->iters, f, h->stream));
+    HCHK(h, launch_fwd_prune(h->kind, h->iters, f, h->stream));
   }
   s = run_group(h, (size_t)n * R);
   if (s != GRAND_OK) return s;
@@ -797,7 +799,10 @@ grand_status grand_create(const grand_params *p, grand_index **out) {
   h->mips = p->metric == GRAND_MIPS;
   h->sdim = p->dim + (h->mips ? 1 : 0);
   h->row_bytes = (size_t)p->dim * h->esize;
-  h->stride = ((size_t)h->sdim * h->esize + 15) / 16 * 16;
+  h->q_stride = ((size_t)h->sdim * h->esize + 15) / 16 * 16;
+  // uint8 pool rows are whole 64-byte matrix-core steps (and so start on the
+  // lines they are read in)
+  h->stride = p->dtype == GRAND_U8 ? (h->q_stride + 63) / 64 * 64 : h->q_stride;
   h->nch = (int)(h->stride / 16);
   h->vc = vec_class(h->nch);
   if (h->vc < 0) {
@@ -817,7 +822,7 @@ grand_status grand_create(const grand_params *p, grand_index **out) {
   P.R = p->R;
   P.cap = p->capacity;
   P.adjd = nullptr;
-  const bool stored = p->algo == GRAND_VAMANA && adj_dists_apply(h->kind, p->R, h->nch, p->P);
+  const bool stored = p->algo == GRAND_VAMANA;
   bool bad = dalloc(&P.vecs, cap * h->stride) || dalloc(&P.adj, cap * p->R) || dalloc(&P.deg, cap) ||
              (stored && dalloc(&P.adjd, cap * p->R)) ||
              dalloc(&P.active, cap) || dalloc(&h->in_batch, cap) || dalloc(&h->bidx, cap) ||
@@ -902,7 +907,7 @@ grand_status grand_insert_batch(grand_index *h, const void *vecs, const uint32_t
   {
     Phase ph(h, GRAND_PH_VALIDATE);
     HCHK(h, hipMemcpyAsync(h->b_ids, ids, (size_t)n * 4, hipMemcpyDefault, h->stream));
-    if ((s = stage_rows(h, h->b_vecs, vecs, n)) != GRAND_OK) return s;
+    if ((s = stage_rows(h, h->b_vecs, h->stride, vecs, n)) != GRAND_OK) return s;
     if ((s = clear_errors(h)) != GRAND_OK) return s;
     h->epoch++;
     HCHK(h, launch_validate_ids(h->b_ids, n, h->p.capacity, h->pool.active, h->mark, h->epoch, 0, h->ds, h->stream));
@@ -998,7 +1003,7 @@ grand_status grand_build_cagra(grand_index *h, const void *vecs, const uint32_t 
     Phase ph(h, GRAND_PH_VALIDATE);
     HCHK(h, hipMemcpyAsync(h->b_ids, ids, (size_t)n * 4, hipMemcpyDefault, h->stream));
     HCHK(h, hipMemcpyAsync(b.init, init, nk * 4, hipMemcpyDefault, h->stream));
-    if ((s = stage_rows(h, h->b_vecs, vecs, n)) != GRAND_OK) return s;
+    if ((s = stage_rows(h, h->b_vecs, h->stride, vecs, n)) != GRAND_OK) return s;
     if ((s = clear_errors(h)) != GRAND_OK) return s;
     h->epoch++;
     HCHK(h, launch_validate_ids(h->b_ids, n, h->p.capacity, h->pool.active, h->mark, h->epoch, 0, h->ds, h->stream));
@@ -1110,15 +1115,15 @@ grand_status grand_search(grand_index *h, const void *queries, uint32_t nq, uint
   if ((s = ensure_query(h, nq, k)) != GRAND_OK) return s;
   if (h->p.dtype == GRAND_F32) {
     Phase ph(h, GRAND_PH_VALIDATE);
-    if ((s = stage_rows(h, h->q_vecs, queries, nq)) != GRAND_OK) return s;
+    if ((s = stage_rows(h, h->q_vecs, h->q_stride, queries, nq)) != GRAND_OK) return s;
     if ((s = clear_errors(h)) != GRAND_OK) return s;
-    HCHK(h, launch_check_finite(h->q_vecs, nq, h->stride, h->p.dim, h->ds, h->stream));
+    HCHK(h, launch_check_finite(h->q_vecs, nq, h->q_stride, h->p.dim, h->ds, h->stream));
     if ((s = read_validation(h)) != GRAND_OK) {
       (void)finish(h);
       return s;
     }
   } else {
-    if ((s = stage_rows(h, h->q_vecs, queries, nq)) != GRAND_OK) return s;
+    if ((s = stage_rows(h, h->q_vecs, h->q_stride, queries, nq)) != GRAND_OK) return s;
   }
   if (h->n_active == 0) {
     HCHK(h, launch_fill_u32(h->q_ids, GRAND_INVALID, (size_t)nq * k, h->stream));
@@ -1128,6 +1133,8 @@ grand_status grand_search(grand_index *h, const void *queries, uint32_t nq, uint
     SearchArgs a{};
     a.pool = h->pool;
     a.qbase = h->q_vecs;
+    a.q_stride = h->q_stride;
+    a.q_nch = (int)(h->q_stride / 16);
     a.nq = nq;
     a.start = h->medoid;
     a.ell = beam;
@@ -1153,9 +1160,9 @@ grand_status grand_search_static(grand_index *h, const void *queries, uint32_t n
   if (k == 0 || beam == 0 || k > beam || beam > 256) return fail(h, GRAND_E_ARG, "need 1 <= k <= beam <= 256");
   if (nq == 0) return GRAND_OK;
   if (!queries || !out_ids || !out_dists) return fail(h, GRAND_E_ARG, "null argument");
-  // layout in `scratch`: query rows (nq x stride), ids (nq x k), distances
+  // layout in `scratch`: query rows (nq x q_stride), ids (nq x k), distances
   // (nq x k), each region 256-byte aligned
-  const size_t qb = ((size_t)nq * h->stride + 255) / 256 * 256;
+  const size_t qb = ((size_t)nq * h->q_stride + 255) / 256 * 256;
   const size_t rb = ((size_t)nq * k * 4 + 255) / 256 * 256;
   if (qb + 2 * rb > kStaticScratchBytes)
     return fail(h, GRAND_E_CAPACITY, "queries and results exceed the static search scratch");
@@ -1164,12 +1171,12 @@ grand_status grand_search_static(grand_index *h, const void *queries, uint32_t n
   uint32_t *q_ids = reinterpret_cast<uint32_t *>(h->static_scratch + qb);
   float *q_d = reinterpret_cast<float *>(h->static_scratch + qb + rb);
   // the array keeps the previous call's contents: zero the rows' padding
-  if (h->stride != h->row_bytes) HCHK(h, launch_fill_u32(reinterpret_cast<uint32_t *>(q_vecs), 0u, qb / 4, h->stream));
-  HCHK(h, copy_rows(q_vecs, h->stride, queries, h->row_bytes, nq, nullptr, h->static_scratch + qb + 2 * rb,
+  if (h->q_stride != h->row_bytes) HCHK(h, launch_fill_u32(reinterpret_cast<uint32_t *>(q_vecs), 0u, qb / 4, h->stream));
+  HCHK(h, copy_rows(q_vecs, h->q_stride, queries, h->row_bytes, nq, nullptr, h->static_scratch + qb + 2 * rb,
                     kStaticScratchBytes - qb - 2 * rb, h->stream));
   if (h->p.dtype == GRAND_F32) {
     if ((s = clear_errors(h)) != GRAND_OK) return s;
-    HCHK(h, launch_check_finite(q_vecs, nq, h->stride, h->p.dim, h->ds, h->stream));
+    HCHK(h, launch_check_finite(q_vecs, nq, h->q_stride, h->p.dim, h->ds, h->stream));
     if ((s = read_validation(h)) != GRAND_OK) {
       (void)finish(h);
       return s;
@@ -1182,6 +1189,8 @@ grand_status grand_search_static(grand_index *h, const void *queries, uint32_t n
     SearchArgs a{};
     a.pool = h->pool;
     a.qbase = q_vecs;
+    a.q_stride = h->q_stride;
+    a.q_nch = (int)(h->q_stride / 16);
     a.nq = nq;
     a.start = h->medoid;
     a.ell = beam;
@@ -1326,19 +1335,19 @@ grand_status grand_reader_search(grand_reader *r, const void *queries, uint32_t 
     const uint32_t nc = std::max(nq, r->qcap), kc = std::max(k, r->qk);
     dfree(r->q_vecs); dfree(r->q_ids); dfree(r->q_d);
     r->qcap = r->qk = 0;
-    if (dalloc(&r->q_vecs, (size_t)nc * h->stride) || dalloc(&r->q_ids, (size_t)nc * kc) ||
+    if (dalloc(&r->q_vecs, (size_t)nc * h->q_stride) || dalloc(&r->q_ids, (size_t)nc * kc) ||
         dalloc(&r->q_d, (size_t)nc * kc)) {
       (void)hipGetLastError();
       return rfail(r, GRAND_E_OOM, "device allocation of reader buffers failed");
     }
-    RCHK(r, hipMemsetAsync(r->q_vecs, 0, (size_t)nc * h->stride, r->stream));
+    RCHK(r, hipMemsetAsync(r->q_vecs, 0, (size_t)nc * h->q_stride, r->stream));
     r->qcap = nc;
     r->qk = kc;
   }
-  RCHK(r, copy_rows(r->q_vecs, h->stride, queries, h->row_bytes, nq, &r->rows, nullptr, 0, r->stream));
+  RCHK(r, copy_rows(r->q_vecs, h->q_stride, queries, h->row_bytes, nq, &r->rows, nullptr, 0, r->stream));
   if (h->p.dtype == GRAND_F32) {
     RCHK(r, launch_fill_u32(&r->ds->err_code, 0u, 2, r->stream));
-    RCHK(r, launch_check_finite(r->q_vecs, nq, h->stride, h->p.dim, r->ds, r->stream));
+    RCHK(r, launch_check_finite(r->q_vecs, nq, h->q_stride, h->p.dim, r->ds, r->stream));
     RCHK(r, hipMemcpyAsync(r->hs, r->ds, kScalarBytes, hipMemcpyDeviceToHost, r->stream));
     RCHK(r, hipStreamSynchronize(r->stream));
     if (r->hs->err_code) return rfail(r, GRAND_E_ARG, "a query holds a non-finite element");
@@ -1346,6 +1355,8 @@ grand_status grand_reader_search(grand_reader *r, const void *queries, uint32_t 
   SearchArgs a{};
   a.pool = h->pool;
   a.qbase = r->q_vecs;
+  a.q_stride = h->q_stride;
+  a.q_nch = (int)(h->q_stride / 16);
   a.nq = nq;
   a.start = GRAND_INVALID;
   a.start_ptr = &h->ds->medoid;  // the index's medoid as the search starts
@@ -1440,7 +1451,7 @@ grand_status grand_import_graph(grand_index *h, const void *vecs, const uint32_t
   if (!vecs || !adj || !deg || !active) return fail(h, GRAND_E_ARG, "null argument");
   HCHK(h, hipSetDevice(h->p.device));
   const size_t cap = h->p.capacity;
-  if ((s = stage_rows(h, h->pool.vecs, vecs, cap)) != GRAND_OK) return s;
+  if ((s = stage_rows(h, h->pool.vecs, h->stride, vecs, cap)) != GRAND_OK) return s;
   HCHK(h, hipMemcpyAsync(h->pool.adj, adj, cap * h->p.R * 4, hipMemcpyDefault, h->stream));
   HCHK(h, hipMemcpyAsync(h->pool.deg, deg, cap * 4, hipMemcpyDefault, h->stream));
   HCHK(h, hipMemcpyAsync(h->pool.active, active, cap, hipMemcpyDefault, h->stream));

@@ -35,21 +35,6 @@
     }                                                                                       \
   } while (0)
 
-// The same for uint8 rows only.
-#define GR_DISPATCH_VC_U8(vc, ...)                                                          \
-  do {                                                                                      \
-    const int v__ = (vc);                                                                   \
-    if (v__ == ::gr::kVcA) {                                                                \
-      constexpr int KIND = ::gr::kU8L2, LPV = 8, CPL = 1; __VA_ARGS__;                      \
-    } else if (v__ == ::gr::kVcB) {                                                         \
-      constexpr int KIND = ::gr::kU8L2, LPV = 8, CPL = 4; __VA_ARGS__;                      \
-    } else if (v__ == ::gr::kVcC) {                                                         \
-      constexpr int KIND = ::gr::kU8L2, LPV = 16, CPL = 16; __VA_ARGS__;                    \
-    } else {                                                                                \
-      return hipErrorInvalidValue;                                                          \
-    }                                                                                       \
-  } while (0)
-
 // Register rows (64 keys each) needed to hold `n` keys: 1, 2 or 4.
 #define GR_DISPATCH_N(n, ...)                                                               \
   do {                                                                                      \

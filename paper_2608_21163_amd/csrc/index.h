@@ -75,8 +75,8 @@ struct PoolView {
   uint32_t *adj;
   uint32_t *deg;
   uint8_t *active;
-  float *adjd;     // Dist(u, N_out(u)[s]) beside every list entry, when stored (else null)
-  size_t stride;   // bytes per pool row (multiple of 16)
+  float *adjd;     // Dist(u, N_out(u)[s]) beside every list entry of a Vamana pool (CAGRA: null)
+  size_t stride;   // bytes per pool row (a multiple of 16; of 64 for uint8 rows)
   int nch;         // 16-byte chunks per row
   uint32_t R;
   uint32_t cap;
@@ -84,7 +84,9 @@ struct PoolView {
 
 struct SearchArgs {
   PoolView pool;
-  const uint8_t *qbase;       // query rows (padded to the pool stride) ...
+  const uint8_t *qbase;       // query rows of q_stride bytes, q_nch 16-byte chunks ...
+  size_t q_stride;
+  int q_nch;
   const uint32_t *qids;       // ... or pool ids used as queries (if non-null)
   uint32_t nq;
   uint32_t start;
@@ -239,9 +241,8 @@ struct CagraArgs {
 int vec_class(int nch);
 hipError_t launch_search(int kind, int vc, const SearchArgs &a, hipStream_t s);
 hipError_t launch_bootstrap(int kind, int vc, const BootArgs &a, hipStream_t s);
-hipError_t launch_fwd_prune(int kind, int vc, uint32_t max_iters, const FwdPruneArgs &a, hipStream_t s);
-hipError_t launch_rebuild(int kind, int vc, uint32_t R, uint32_t P, const RebuildArgs &a, uint32_t grid,
-                          hipStream_t s);
+hipError_t launch_fwd_prune(int kind, uint32_t max_iters, const FwdPruneArgs &a, hipStream_t s);
+hipError_t launch_rebuild(int kind, uint32_t R, uint32_t P, const RebuildArgs &a, uint32_t grid, hipStream_t s);
 hipError_t launch_repair(int kind, int vc, const RepairArgs &a, uint32_t grid, hipStream_t s);
 hipError_t launch_repair_plan(const RepairArgs &a, uint32_t *counts, uint32_t *chunks, hipStream_t s);
 hipError_t launch_repair_map(const RepairArgs &a, uint4 *cdesc, hipStream_t s);
@@ -259,11 +260,6 @@ hipError_t launch_mips_augment(uint8_t *rows, size_t n, size_t stride, uint32_t 
                                hipStream_t s);
 hipError_t launch_check_finite(const uint8_t *rows, uint32_t n, size_t stride, uint32_t dim, DevScalars *ds,
                                hipStream_t s);
-// Stored list distances apply to Vamana pools whose list writers are the
-// forward prune and rebuild kernels that maintain them: fp32 ones, and uint8
-// ones with R <= 64, R a multiple of 4, rows of 64 or 128 bytes, P <= 64 and
-// R + P <= 128.
-bool adj_dists_apply(int kind, uint32_t R, int nch, uint32_t P);
 // Dist(u, v) for every entry of every list (after a bulk import).
 hipError_t launch_adj_dists(PoolView p, int kind, hipStream_t s);
 hipError_t launch_stage(PoolView p, const uint8_t *rows, const uint32_t *ids, uint32_t n, uint32_t *bidx,

@@ -1,389 +1,13 @@
-// k_prune.hip -- GrANDRobustPrune (Alg. 4) executed by one wavefront, the
-// forward prune of new nodes (Alg. 5, second loop) and the rebuild of every
-// dirty node (Alg. 5 and Alg. 6, last loops), one wavefront per node.
+// k_prune.hip -- the forward prune of new nodes (Alg. 5, second loop) and the
+// rebuild of every dirty node (Alg. 5 and Alg. 6, last loops) by
+// GrANDRobustPrune (Alg. 4), one wavefront per node.
 //
-// When the candidate rows fit, a node's candidates and its own row are
-// staged into LDS once (all gathers in flight together), and every distance
-// of the prune -- D_p and the pairwise distances of the selection loop -- is
-// evaluated from LDS.  LDS slots are assigned in ascending id order, so
-// ordering keys by (distance, slot) breaks ties exactly as (distance, id).
-// Rows too long for LDS are read from global memory (L2) instead.
+// The rebuild of uint8 rows of 64 or 128 bytes keeps the candidate tiles in
+// registers (k_rebuild_mr); forward prunes, every other row length, fp32 rows,
+// and scratch capacities above 64 take prune_gram (gram.h).
 #include "gram.h"
 
 namespace gr {
-
-// GrANDRobustPrune of node p over candidates addressed as rows of `vecs`.
-// Candidates (any order, invalid padded) come with their distances D_p.
-// They are sorted by (D_p, address); repeats and p itself are dropped.  The
-// first valid candidate p* is selected; selection stops at R; otherwise the
-// distance from p* to every later valid candidate p' is evaluated by the
-// wave (pivot p* held in registers, candidate rows LPV lanes per row) and p'
-// is invalidated when coef * Dist(p*, p') <= D_p[p'] (coef is alpha, or
-// alpha^2 for the Euclidean reading, compared in fp64).
-// On return lane t < nsel holds the t-th selection (address, distance).
-template <int KIND, int LPV, int CPL, int NR>
-__device__ int wave_prune(const uint8_t *vecs, size_t stride, int nch, uint32_t p, uint32_t R, double coef,
-                          float (&cd)[NR], uint32_t (&ci)[NR], uint32_t *lids, float *ldist, uint32_t &sel_id,
-                          float &sel_d, unsigned long long &evals) {
-  const int ln = lane();
-#pragma unroll
-  for (int r = 0; r < NR; r++)
-    if ((ci[r] & kIdMask) == p || !kvalid(ci[r])) { cd[r] = finf(); ci[r] = kInvalid; }
-  wave_sort<NR>(cd, ci);
-  uint64_t dm[NR];
-  if (wave_find_repeats<NR>(cd, ci, dm)) {
-#pragma unroll
-    for (int r = 0; r < NR; r++)
-      if ((dm[r] >> ln) & 1) { cd[r] = finf(); ci[r] = kInvalid; }
-    wave_sort<NR>(cd, ci);
-  }
-  bool valid[NR];
-#pragma unroll
-  for (int r = 0; r < NR; r++) valid[r] = kvalid(ci[r]);
-  sel_id = kInvalid;
-  sel_d = finf();
-  int nsel = 0;
-  while (nsel < (int)R) {
-    int e = -1;
-#pragma unroll
-    for (int r = 0; r < NR; r++) {
-      const uint64_t m = ballot(valid[r]);
-      if (e < 0 && m) e = r * 64 + ffs64(m);
-    }
-    if (e < 0) break;
-    const int er = e >> 6, el = e & 63;
-    uint32_t pid = 0;
-    float pd = 0.0f;
-#pragma unroll
-    for (int r = 0; r < NR; r++)
-      if (r == er) {
-        pid = rdlane(ci[r], el);
-        pd = rdlane(cd[r], el);
-        if (ln == el) valid[r] = false;
-      }
-    if (ln == nsel) { sel_id = pid; sel_d = pd; }
-    nsel++;
-    if (nsel == (int)R) break;
-    // compact the remaining valid candidates (all lie after p*)
-    int cnt = 0;
-    int cidx[NR];
-#pragma unroll
-    for (int r = 0; r < NR; r++) {
-      const uint64_t m = ballot(valid[r]);
-      cidx[r] = cnt + mbcnt(m);
-      if (valid[r]) lids[cidx[r]] = ci[r];
-      cnt += popc(m);
-    }
-    if (cnt == 0) break;
-    Slice<KIND, LPV, CPL> s;
-    load_slice<KIND, LPV, CPL>(s, vecs + (size_t)pid * stride, nch);
-    __syncthreads();
-    wave_dists<KIND, LPV, CPL>(s, vecs, stride, nch, lids, ldist, cnt);
-    __syncthreads();
-    evals += (unsigned long long)cnt;
-#pragma unroll
-    for (int r = 0; r < NR; r++)
-      if (valid[r] && coef * (double)ldist[cidx[r]] <= (double)cd[r]) valid[r] = false;
-    __syncthreads();
-  }
-  return nsel;
-}
-
-// Bytes per LDS row: the pool stride plus one chunk, which staggers rows
-// across LDS banks.
-__host__ __device__ constexpr size_t lds_stride(size_t stride) { return stride + 16; }
-
-// Copies rows ids[0..m) and row `extra` (slot m) of the pool into LDS slots
-// 0..m, LPV lanes per row, with the gathers of RIF row groups in flight.
-template <int LPV, int CPL>
-__device__ __forceinline__ void stage_rows(const PoolView &P, const uint32_t *ids, int m, uint32_t extra,
-                                           uint8_t *vbuf) {
-  constexpr int G = 64 / LPV;
-  constexpr int RIF = CPL >= 8 ? 1 : 8 / CPL;
-  const int ln = lane(), grp = ln / LPV, sub = ln % LPV;
-  const size_t ls = lds_stride(P.stride);
-  for (int base = 0; base <= m; base += G * RIF) {
-    uint4 b[RIF][CPL];
-#pragma unroll
-    for (int rr = 0; rr < RIF; rr++) {
-      const int e = base + rr * G + grp;
-      const uint32_t id = e < m ? ids[e] : extra;
-      const uint8_t *row = P.vecs + (size_t)id * P.stride;
-#pragma unroll
-      for (int k = 0; k < CPL; k++) {
-        const int ch = sub + k * LPV;
-        b[rr][k] = (e <= m && ch < P.nch) ? ld16(row + (size_t)ch * 16) : make_uint4(0, 0, 0, 0);
-      }
-    }
-#pragma unroll
-    for (int rr = 0; rr < RIF; rr++) {
-      const int e = base + rr * G + grp;
-#pragma unroll
-      for (int k = 0; k < CPL; k++) {
-        const int ch = sub + k * LPV;
-        if (e <= m && ch < P.nch) *reinterpret_cast<uint4 *>(vbuf + (size_t)e * ls + (size_t)ch * 16) = b[rr][k];
-      }
-    }
-  }
-}
-
-// GrANDRobustPrune of node p over the m distinct candidate ids in slot_id
-// (LDS, any order), with every vector in LDS: the ids are sorted (slot =
-// rank of the id), the rows of the candidates and of p are staged, D_p is
-// evaluated from LDS (bit-identical to the distance evaluated during the
-// search or carried by the records: the arithmetic and lane layout are the
-// same), and the selection loop runs on LDS rows.  Lane t < nsel returns the
-// t-th selected id and its distance.
-template <int KIND, int LPV, int CPL, int NC>
-__device__ int prune_staged(const PoolView &P, uint32_t p, int m, uint32_t R, double coef, uint32_t *slot_id,
-                            uint8_t *vbuf, uint32_t *lids, float *ldist, uint32_t &sel_id, float &sel_d,
-                            unsigned long long &evals) {
-  const int ln = lane();
-  const size_t ls = lds_stride(P.stride);
-  float kd[NC];
-  uint32_t kid[NC];
-#pragma unroll
-  for (int r = 0; r < NC; r++) {
-    const int e = r * 64 + ln;
-    kd[r] = e < m ? 0.0f : finf();
-    kid[r] = e < m ? slot_id[e] : kInvalid;
-  }
-  wave_sort<NC>(kd, kid);
-  __syncthreads();
-#pragma unroll
-  for (int r = 0; r < NC; r++) {
-    const int e = r * 64 + ln;
-    if (e < m) {
-      slot_id[e] = kid[r];
-      lids[e] = (uint32_t)e;
-    }
-  }
-  __syncthreads();
-  stage_rows<LPV, CPL>(P, slot_id, m, p, vbuf);
-  __syncthreads();
-  Slice<KIND, LPV, CPL> su;
-  load_slice<KIND, LPV, CPL>(su, vbuf + (size_t)m * ls, P.nch);
-  wave_dists<KIND, LPV, CPL>(su, vbuf, ls, P.nch, lids, ldist, m);
-  __syncthreads();
-  evals += (unsigned long long)m;
-  float cd[NC];
-  uint32_t ci[NC];
-#pragma unroll
-  for (int r = 0; r < NC; r++) {
-    const int e = r * 64 + ln;
-    cd[r] = e < m ? ldist[e] : finf();
-    ci[r] = e < m ? (uint32_t)e : kInvalid;
-  }
-  __syncthreads();
-  uint32_t ssl;
-  const int nsel = wave_prune<KIND, LPV, CPL, NC>(vbuf, ls, P.nch, kIdMask - 1, R, coef, cd, ci, lids, ldist, ssl,
-                                                  sel_d, evals);
-  sel_id = ln < nsel ? slot_id[ssl] : kInvalid;
-  __syncthreads();
-  return nsel;
-}
-
-// ---------------------------------------------------------------------------
-// uint8 GrANDRobustPrune on the matrix cores.  Rows are staged in LDS as in
-// prune_staged.  The pairwise distances of the candidates form a dense Gram
-// matrix (m x m x dim): with y = x - 128 (byte-wise x ^ 0x80, an exact int8
-// view), Dist(i, j) = |y_i|^2 + |y_j|^2 - 2 y_i.y_j exactly in int32 (L2 is
-// translation invariant), so the products run on v_mfma_i32_16x16x64_i8.
-// Candidates are ordered by (D_p, slot); the greedy selection walks them in
-// blocks of 16 pivots: a block's distance rows to every later candidate are
-// produced by MFMA into LDS (blocks without a valid pivot are skipped), then
-// the block's pivots are taken in order, each invalidating later candidates
-// with coef * Dist(p*, p') <= D_p[p'].  Requires dim to be a multiple of 64.
-struct MfmaLds {
-  uint32_t *slot_id;   // [64*NC] candidate ids, then sorted by id (slot order)
-  int32_t *nrm;        // [64*NC + 1] |y|^2 per slot (slot m = the node)
-  float *dpos;         // [64*NC] D_p by sorted position
-  uint32_t *spos;      // [64*NC] slot by sorted position
-  float *blk;          // [16][64*NC] distance rows of the current pivot block
-  uint8_t *vbuf;       // [(64*NC + 1) * lds_stride] rows
-};
-
-// Dynamic LDS of the matrix-core prune for up to MP candidates:
-// blk | nrm | rows.
-__host__ __device__ constexpr size_t mfma_blk_bytes(int MP) { return (size_t)16 * MP * 4; }
-__host__ __device__ constexpr size_t mfma_nrm_bytes(int MP) { return ((size_t)(MP + 1) * 4 + 15) / 16 * 16; }
-__host__ __device__ constexpr size_t mfma_lds_bytes(size_t stride, int MP) {
-  return mfma_blk_bytes(MP) + mfma_nrm_bytes(MP) + (size_t)(MP + 1) * lds_stride(stride);
-}
-__device__ __forceinline__ MfmaLds mfma_lds(uint8_t *dyn, uint32_t *slot_id, uint32_t *spos, float *dpos, int MP) {
-  MfmaLds L;
-  L.slot_id = slot_id;
-  L.spos = spos;
-  L.dpos = dpos;
-  L.blk = reinterpret_cast<float *>(dyn);
-  L.nrm = reinterpret_cast<int32_t *>(dyn + mfma_blk_bytes(MP));
-  L.vbuf = dyn + mfma_blk_bytes(MP) + mfma_nrm_bytes(MP);
-  return L;
-}
-
-template <int LPV, int CPL, int NC>
-__device__ int prune_mfma_u8(const PoolView &P, uint32_t p, int m, uint32_t R, double coef, const MfmaLds &L,
-                             uint32_t &sel_id, float &sel_d, unsigned long long &evals) {
-  constexpr int MP = 64 * NC;
-  const int ln = lane();
-  const size_t ls = lds_stride(P.stride);
-  const int nk = P.nch / 4;  // 64-byte K chunks
-  sel_id = kInvalid;
-  sel_d = finf();
-  if (m <= 0) return 0;
-  // slots in ascending id order
-  {
-    float kd[NC];
-    uint32_t kid[NC];
-#pragma unroll
-    for (int r = 0; r < NC; r++) {
-      const int e = r * 64 + ln;
-      kd[r] = e < m ? 0.0f : finf();
-      kid[r] = e < m ? L.slot_id[e] : kInvalid;
-    }
-    wave_sort<NC>(kd, kid);
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < NC; r++)
-      if (r * 64 + ln < m) L.slot_id[r * 64 + ln] = kid[r];
-    __syncthreads();
-  }
-  stage_rows<LPV, CPL>(P, L.slot_id, m, p, L.vbuf);
-  __syncthreads();
-  // |y|^2 per slot and D_p = |y_p|^2 + |y_j|^2 - 2 y_p.y_j (exact)
-  const uint8_t *prow = L.vbuf + (size_t)m * ls;
-  int np = 0;
-  for (int c = 0; c < P.nch; c++) {
-    const uint4 v = ld16(prow + (size_t)c * 16);
-    const uint32_t a0 = v.x ^ 0x80808080u, a1 = v.y ^ 0x80808080u, a2 = v.z ^ 0x80808080u, a3 = v.w ^ 0x80808080u;
-    np = sdot4(a0, a0, np); np = sdot4(a1, a1, np); np = sdot4(a2, a2, np); np = sdot4(a3, a3, np);
-  }
-  float kd[NC];
-  uint32_t kid[NC];
-#pragma unroll
-  for (int r = 0; r < NC; r++) {
-    const int e = r * 64 + ln;
-    kd[r] = finf();
-    kid[r] = kInvalid;
-    if (e < m) {
-      const uint8_t *row = L.vbuf + (size_t)e * ls;
-      int nn = 0, dp = 0;
-      for (int c = 0; c < P.nch; c++) {
-        const uint4 v = ld16(row + (size_t)c * 16), w = ld16(prow + (size_t)c * 16);
-        const uint32_t a0 = v.x ^ 0x80808080u, a1 = v.y ^ 0x80808080u, a2 = v.z ^ 0x80808080u, a3 = v.w ^ 0x80808080u;
-        nn = sdot4(a0, a0, nn); nn = sdot4(a1, a1, nn); nn = sdot4(a2, a2, nn); nn = sdot4(a3, a3, nn);
-        dp = sdot4(a0, w.x ^ 0x80808080u, dp); dp = sdot4(a1, w.y ^ 0x80808080u, dp);
-        dp = sdot4(a2, w.z ^ 0x80808080u, dp); dp = sdot4(a3, w.w ^ 0x80808080u, dp);
-      }
-      L.nrm[e] = nn;
-      kd[r] = canon0((float)(np + nn - 2 * dp));
-      kid[r] = (uint32_t)e;
-    }
-  }
-  evals += (unsigned long long)m;
-  wave_sort<NC>(kd, kid);
-  bool valid[NC];
-#pragma unroll
-  for (int r = 0; r < NC; r++) {
-    const int e = r * 64 + ln;
-    valid[r] = e < m;
-    L.spos[e] = kid[r];
-    L.dpos[e] = kd[r];
-  }
-  __syncthreads();
-  const int nt = (m + 15) / 16;
-  int nsel = 0;
-  bool done = false;
-  for (int b = 0; b < nt && !done; b++) {
-    // Sorted positions 16c .. 16c+15 (tile c) live in register row c/4,
-    // lanes 16*(c%4) ..; tmask marks the tiles that still hold a valid
-    // candidate, vb the valid pivots of block b.
-    uint64_t vb = 0;
-    uint32_t tmask = 0;
-#pragma unroll
-    for (int r = 0; r < NC; r++) {
-      const uint64_t vm = ballot(valid[r]);
-#pragma unroll
-      for (int q = 0; q < 4; q++)
-        if ((vm >> (16 * q)) & 0xFFFFull) tmask |= 1u << (4 * r + q);
-      if (r == b / 4) vb = (vm >> (16 * (b % 4))) & 0xFFFFull;
-    }
-    if (!vb) continue;
-    // distance rows of the block's candidates to every candidate of tile c >= b
-    const int arow = 16 * b + (ln & 15);
-    const uint32_t aslot = L.spos[arow < m ? arow : 0];
-    const int kb = ln >> 4;
-    for (int c = b; c < nt; c++) {
-      if (!((tmask >> c) & 1u)) continue;
-      const int bcol = 16 * c + (ln & 15);
-      const uint32_t bslot = L.spos[bcol < m ? bcol : 0];
-      v4i acc = {0, 0, 0, 0};
-      for (int kk = 0; kk < nk; kk++) {
-        const uint4 av = ld16(L.vbuf + (size_t)aslot * ls + (size_t)kk * 64 + (size_t)kb * 16);
-        const uint4 bv = ld16(L.vbuf + (size_t)bslot * ls + (size_t)kk * 64 + (size_t)kb * 16);
-        v4i A, B;
-        A[0] = (int)(av.x ^ 0x80808080u); A[1] = (int)(av.y ^ 0x80808080u);
-        A[2] = (int)(av.z ^ 0x80808080u); A[3] = (int)(av.w ^ 0x80808080u);
-        B[0] = (int)(bv.x ^ 0x80808080u); B[1] = (int)(bv.y ^ 0x80808080u);
-        B[2] = (int)(bv.z ^ 0x80808080u); B[3] = (int)(bv.w ^ 0x80808080u);
-        acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(A, B, acc, 0, 0, 0);
-      }
-      const int ncol = L.nrm[bslot];
-#pragma unroll
-      for (int i = 0; i < 4; i++) {
-        const int rr = 4 * (ln >> 4) + i;
-        const int rpos = 16 * b + rr;
-        const int rn = L.nrm[L.spos[rpos < m ? rpos : 0]];
-        L.blk[rr * MP + bcol] = canon0((float)(rn + ncol - 2 * acc[i]));
-      }
-    }
-    evals += (unsigned long long)256 * __popc(tmask >> b);
-    __syncthreads();
-    for (int t = 0; t < 16; t++) {
-      const int pos = 16 * b + t;
-      if (pos >= m) break;
-      if (!((vb >> t) & 1)) continue;
-      // recheck: earlier pivots of this block may have invalidated it
-      uint64_t still = 0;
-#pragma unroll
-      for (int r = 0; r < NC; r++) {
-        const uint64_t vm = ballot(valid[r]);
-        if (r == b / 4) still = (vm >> (16 * (b % 4) + t)) & 1ull;
-      }
-      if (!still) continue;
-      if (ln == nsel) { sel_id = L.slot_id[L.spos[pos]]; sel_d = L.dpos[pos]; }
-      nsel++;
-#pragma unroll
-      for (int r = 0; r < NC; r++)
-        if (r * 64 + ln == pos) valid[r] = false;
-      if (nsel == (int)R) { done = true; break; }
-#pragma unroll
-      for (int r = 0; r < NC; r++) {
-        const int j = r * 64 + ln;
-        if (valid[r] && j > pos && coef * (double)L.blk[t * MP + j] <= (double)L.dpos[j]) valid[r] = false;
-      }
-    }
-    __syncthreads();
-  }
-  return nsel;
-}
-
-// The largest integer distance d with coef * d <= D (fp64 product, as in the
-// prune test), for an integer-valued D >= 0; every d up to it passes, since
-// rounding is monotone.
-// inv is 1 / coef (rounded): the quotient estimate is off by at most one,
-// and the two exact tests correct it.
-__device__ __forceinline__ int kill_threshold(double coef, double inv, float D) {
-  if (!(coef > 0.0)) return 0x7FFFFFFF;
-  const double dd = (double)D;
-  if (!(dd < 2147483647.0)) return 0x7FFFFFFF;
-  const double q = floor(dd * inv);
-  if (!(q < 2147483646.0)) return 0x7FFFFFFF;
-  int t = (int)q;
-  t = coef * (double)(t + 1) <= dd ? t + 1 : t;
-  t = coef * (double)t <= dd ? t : t - 1;
-  return t;
-}
 
 // GrANDRobustPrune's greedy selection for uint8 rows of 64*NK bytes, over
 // up to 64*NR candidates already sorted by (D_p, id): spos/dpos (LDS) hold
@@ -656,267 +280,28 @@ __device__ int greedy_u8_reg(const PoolView &P, uint32_t p, int m, uint32_t R, d
 }
 
 // ---------------------------------------------------------------------------
-// Forward GrANDRobustPrune of a new uint8 point (rows of 64*NK bytes, R <=
-// 64): V_i arrives with D_{p_i} from the search, so the keys are sorted at
-// once and the greedy selection (greedy_u8) needs no gather beforehand.
-template <int NK, int NR>
-__global__ __launch_bounds__(64, 6) void k_fwd_prune_mr(FwdPruneArgs a) {
-  __shared__ uint32_t spos[64 * NR];
-  __shared__ float dpos[64 * NR];
-  const int ln = lane();
-  const uint32_t i = blockIdx.x;
-  if (i >= a.n) return;
-  const PoolView &P = a.pool;
-  const uint32_t p = a.ids[i];
-  const uint32_t nv = a.v_n[i];
-  const uint32_t R = P.R;
-  float kd[NR];
-  uint32_t kid[NR];
-#pragma unroll
-  for (int r = 0; r < NR; r++) {
-    const uint32_t e = r * 64 + ln;
-    const bool in = e < nv;
-    uint32_t id = in ? a.v_ids[(size_t)i * a.v_stride + e] : kInvalid;
-    float d = in ? a.v_d[(size_t)i * a.v_stride + e] : finf();
-    if (id == p || !kvalid(id)) { id = kInvalid; d = finf(); }
-    kd[r] = d;
-    kid[r] = id;
-  }
-  wave_sort<NR>(kd, kid);
-  {
-    uint64_t dm[NR];
-    if (wave_find_repeats<NR>(kd, kid, dm)) {
-#pragma unroll
-      for (int r = 0; r < NR; r++)
-        if ((dm[r] >> ln) & 1) { kd[r] = finf(); kid[r] = kInvalid; }
-      wave_sort<NR>(kd, kid);
-    }
-  }
-  bool valid[NR];
-  int m = 0;
-#pragma unroll
-  for (int r = 0; r < NR; r++) {
-    valid[r] = kvalid(kid[r]);
-    m += popc(ballot(valid[r]));
-    spos[r * 64 + ln] = kid[r];
-    dpos[r * 64 + ln] = kd[r];
-  }
-  __syncthreads();
-  uint32_t sid;
-  float sdist;
-  unsigned long long evals = 0;
-  const int nsel = greedy_u8<NK, NR>(P, p, m, R, a.coef, spos, dpos, valid, sid, sdist, evals);
-  if (ln < (int)R) {
-    const bool in = ln < nsel;
-    P.adj[(size_t)p * R + ln] = in ? sid : kInvalid;
-    if (P.adjd) P.adjd[(size_t)p * R + ln] = in ? sdist : 0.0f;
-    a.rec_t[(size_t)i * R + ln] = in ? sid : kInvalid;
-    a.rec_s[(size_t)i * R + ln] = p;
-    a.rec_d[(size_t)i * R + ln] = in ? sdist : 0.0f;
-  }
-  if (ln == 0) {
-    P.deg[p] = (uint32_t)nsel;
-    stat_add(a.ds, kStFwdPrunes, 1ull);
-    stat_add(a.ds, kStFwdEvals, evals);
-    stat_add(a.ds, kStRecords, (unsigned long long)nsel);
-  }
-}
-
-// Forward lists of new nodes: GrANDRobustPrune(p_i, V_i \ {p_i}, D_{p_i}),
-// written to p_i's row (each new node owns its row), and the reverse-edge
-// records (u, p_i, D_{p_i}[u]) for every selected u.
-// MODE: kGlobal (rows read from global memory), kStaged (rows staged in
-// LDS), kMfma (uint8 rows staged in LDS, pairwise distances on MFMA).
-enum { kGlobal = 0, kStaged = 1, kMfma = 2 };
-
-template <int KIND, int LPV, int CPL, int NR, int MODE>
-__global__ __launch_bounds__(64) void k_fwd_prune(FwdPruneArgs a) {
-  extern __shared__ __align__(16) uint8_t vbuf[];
-  __shared__ uint32_t slot_id[64 * NR];
-  __shared__ uint32_t lids[64 * NR];
-  __shared__ float ldist[64 * NR];
-  const int ln = lane();
-  const uint32_t i = blockIdx.x;
-  if (i >= a.n) return;
-  const PoolView &P = a.pool;
-  const uint32_t p = a.ids[i];
-  const uint32_t nv = a.v_n[i];
-  unsigned long long evals = 0;
-  uint32_t sid;
-  float sdist;
-  int nsel;
-  if (MODE != kGlobal) {
-    // V_i holds distinct ids other than p_i
-#pragma unroll
-    for (int r = 0; r < NR; r++) {
-      const uint32_t e = r * 64 + ln;
-      if (e < nv) slot_id[e] = a.v_ids[(size_t)i * a.v_stride + e];
-    }
-    __syncthreads();
-    if constexpr (MODE == kMfma)
-      nsel = prune_mfma_u8<LPV, CPL, NR>(P, p, (int)nv, P.R, a.coef, mfma_lds(vbuf, slot_id, lids, ldist, 64 * NR),
-                                         sid, sdist, evals);
-    else
-      nsel = prune_staged<KIND, LPV, CPL, NR>(P, p, (int)nv, P.R, a.coef, slot_id, vbuf, lids, ldist, sid, sdist,
-                                              evals);
-  } else {
-    float cd[NR];
-    uint32_t ci[NR];
-#pragma unroll
-    for (int r = 0; r < NR; r++) {
-      const uint32_t e = r * 64 + ln;
-      const bool in = e < nv;
-      cd[r] = in ? a.v_d[(size_t)i * a.v_stride + e] : finf();
-      ci[r] = in ? a.v_ids[(size_t)i * a.v_stride + e] : kInvalid;
-    }
-    nsel = wave_prune<KIND, LPV, CPL, NR>(P.vecs, P.stride, P.nch, p, P.R, a.coef, cd, ci, lids, ldist, sid, sdist,
-                                          evals);
-  }
-  if (ln < (int)P.R) {
-    const bool in = ln < nsel;
-    P.adj[(size_t)p * P.R + ln] = in ? sid : kInvalid;
-    a.rec_t[(size_t)i * P.R + ln] = in ? sid : kInvalid;
-    a.rec_s[(size_t)i * P.R + ln] = p;
-    a.rec_d[(size_t)i * P.R + ln] = in ? sdist : 0.0f;
-  }
-  if (ln == 0) {
-    P.deg[p] = (uint32_t)nsel;
-    stat_add(a.ds, kStFwdPrunes, 1ull);
-    stat_add(a.ds, kStFwdEvals, evals);
-    stat_add(a.ds, kStRecords, (unsigned long long)nsel);
-  }
-}
-
 // Rebuild of dirty nodes.  For dirty u: scratch_u = the P smallest distinct
 // (distance, source) records addressed to u; C = (N_out(u) u scratch_u)
 // minus u (and minus the delete batch); if |C| <= R, C is installed (kept
 // entries in slot order, then new sources in record order); otherwise
 // GrANDRobustPrune(u, C, D_u) is installed.  One owner per dirty node, so
 // rows are written without locks.
-template <int KIND, int LPV, int CPL, int NP, int NC, int MODE>
-__global__ __launch_bounds__(64) void k_rebuild(RebuildArgs a) {
-  extern __shared__ __align__(16) uint8_t vbuf[];
-  __shared__ uint32_t rowL[64];
-  __shared__ uint32_t slot_id[64 * NC];
-  __shared__ uint32_t lids[64 * NC];
-  __shared__ float ldist[64 * NC];
-  const int ln = lane();
-  const PoolView &P = a.pool;
-  const uint32_t R = P.R;
-  const uint32_t nd_total = *a.list_n;
-  unsigned long long evals = 0, prunes = 0, nodes = 0, recs = 0, cand = 0;
-  for (uint32_t it = blockIdx.x; it < nd_total; it += gridDim.x) {
-    const uint32_t u = a.list[it];
-    nodes++;
-    const uint32_t g0 = a.goff[u], g1 = a.goff[u + 1];
-    recs += g1 - g0;
-    float sd[NP];
-    uint32_t si[NP];
-#pragma unroll
-    for (int r = 0; r < NP; r++) { sd[r] = finf(); si[r] = kInvalid; }
-    for (uint32_t base = g0; base < g1; base += 64) {
-      const uint32_t j = base + ln;
-      uint32_t sv = j < g1 ? a.gsrc[j] : kInvalid;
-      float dv = j < g1 ? a.gd[j] : finf();
-      if (!kvalid(sv)) { sv = kInvalid; dv = finf(); }
-      wave_merge_new_fast<NP>(sd, si, dv, sv, (int)a.P);
-    }
-    const uint32_t rv = ln < (int)R ? P.adj[(size_t)u * R + ln] : kInvalid;
-    const bool keep = rv != kInvalid && rv != u && !(a.in_batch && a.in_batch[rv]);
-    rowL[ln] = keep ? rv : kInvalid;
-    __syncthreads();
-    bool isnew[NP];
-#pragma unroll
-    for (int r = 0; r < NP; r++) {
-      const uint32_t sv = si[r];
-      bool ok = kvalid(sv) && sv != u && !(a.in_batch && a.in_batch[sv]);
-      for (uint32_t t = 0; t < R; t++) ok = ok && rowL[t] != sv;
-      isnew[r] = ok;
-    }
-    const uint64_t km = ballot(keep);
-    const int kr = popc(km);
-    int kn = 0;
-    int npos[NP];
-#pragma unroll
-    for (int r = 0; r < NP; r++) {
-      const uint64_t mm = ballot(isnew[r]);
-      npos[r] = kn + mbcnt(mm);
-      kn += popc(mm);
-    }
-    const int m = kr + kn;
-    uint32_t *cl = MODE != kGlobal ? slot_id : lids;
-    if (keep) cl[mbcnt(km)] = rv;
-#pragma unroll
-    for (int r = 0; r < NP; r++)
-      if (isnew[r]) {
-        cl[kr + npos[r]] = si[r];
-        if (MODE == kGlobal) ldist[kr + npos[r]] = sd[r];
-      }
-    __syncthreads();
-    if (m <= (int)R) {
-      if (ln < (int)R) P.adj[(size_t)u * R + ln] = ln < m ? cl[ln] : kInvalid;
-      if (ln == 0) P.deg[u] = (uint32_t)m;
-    } else {
-      uint32_t sid;
-      float sdist;
-      int nsel;
-      if constexpr (MODE == kMfma) {
-        nsel = prune_mfma_u8<LPV, CPL, NC>(P, u, m, R, a.coef, mfma_lds(vbuf, slot_id, lids, ldist, 64 * NC), sid,
-                                           sdist, evals);
-      } else if constexpr (MODE == kStaged) {
-        nsel = prune_staged<KIND, LPV, CPL, NC>(P, u, m, R, a.coef, slot_id, vbuf, lids, ldist, sid, sdist, evals);
-      } else {
-        // D_u of kept entries from global rows; new entries carry theirs
-        Slice<KIND, LPV, CPL> s;
-        load_slice<KIND, LPV, CPL>(s, P.vecs + (size_t)u * P.stride, P.nch);
-        wave_dists<KIND, LPV, CPL>(s, P.vecs, P.stride, P.nch, lids, ldist, kr);
-        evals += (unsigned long long)kr;
-        __syncthreads();
-        float cd[NC];
-        uint32_t ci[NC];
-#pragma unroll
-        for (int r = 0; r < NC; r++) {
-          const int e = r * 64 + ln;
-          cd[r] = e < m ? ldist[e] : finf();
-          ci[r] = e < m ? lids[e] : kInvalid;
-        }
-        __syncthreads();
-        nsel = wave_prune<KIND, LPV, CPL, NC>(P.vecs, P.stride, P.nch, u, R, a.coef, cd, ci, lids, ldist, sid, sdist,
-                                              evals);
-      }
-      if (ln < (int)R) P.adj[(size_t)u * R + ln] = ln < nsel ? sid : kInvalid;
-      if (ln == 0) P.deg[u] = (uint32_t)nsel;
-      prunes++;
-      cand += (unsigned long long)m + 1;
-    }
-    __syncthreads();
-  }
-  if (ln == 0) {
-    stat_add(a.ds, kStRbPrunes, prunes);
-    stat_add(a.ds, kStRbEvals, evals);
-    stat_add(a.ds, kStRbCand, cand);
-    if (a.count_nodes) {
-      stat_add(a.ds, kStDirty, nodes);
-      stat_add(a.ds, kStRbRecs, recs);
-    }
-  }
-}
 
 // C of dirty node u (R <= 64, P <= 64 * NP): the kept entries of N_out(u)
 // (minus u and the delete batch) in slot order, then the sources of the P
-// smallest distinct records that are not already kept; written to cl (LDS),
-// and with cdl (LDS, given when the pool stores list distances) D_u of each:
-// the stored distance of a kept entry, the record's distance of a new one.
+// smallest distinct records that are not already kept, written to cl (LDS),
+// with D_u of each in cdl (LDS): the stored distance of a kept entry, the
+// record's distance of a new one.
 // Returns |C|; nrec is the number of records addressed to u.
 template <int NP>
 __device__ int collect_candidates(const RebuildArgs &a, uint32_t u, uint4 *rowL, uint32_t *cl, uint32_t &nrec,
-                                  float *cdl = nullptr) {
+                                  float *cdl) {
   const int ln = lane();
   const PoolView &P = a.pool;
   const uint32_t R = P.R;
   const uint32_t g0 = a.goff[u], g1 = a.goff[u + 1];
   const uint32_t rv = ln < (int)R ? P.adj[(size_t)u * R + ln] : kInvalid;
-  const float rdv = cdl && ln < (int)R ? P.adjd[(size_t)u * R + ln] : 0.0f;
+  const float rdv = ln < (int)R ? P.adjd[(size_t)u * R + ln] : 0.0f;
   nrec = g1 - g0;
   // the first 64 records, loaded beside the row (lanes past the records
   // read a valid one and drop it); then the batch flags of the row's ids and
@@ -944,7 +329,7 @@ __device__ int collect_candidates(const RebuildArgs &a, uint32_t u, uint4 *rowL,
   reinterpret_cast<uint32_t *>(rowL)[ln] = keep ? rv : kInvalid;
   if (keep) {
     cl[mbcnt(kmask)] = rv;
-    if (cdl) cdl[mbcnt(kmask)] = rdv;
+    cdl[mbcnt(kmask)] = rdv;
   }
   __syncthreads();
   // scratch_u: the P smallest distinct (distance, source) records
@@ -974,7 +359,7 @@ __device__ int collect_candidates(const RebuildArgs &a, uint32_t u, uint4 *rowL,
     const uint64_t nmask = ballot(isnew);
     if (isnew) {
       cl[m + mbcnt(nmask)] = sv;
-      if (cdl) cdl[m + mbcnt(nmask)] = sd[r];
+      cdl[m + mbcnt(nmask)] = sd[r];
     }
     m += popc(nmask);
   }
@@ -986,30 +371,25 @@ __device__ int collect_candidates(const RebuildArgs &a, uint32_t u, uint4 *rowL,
 // up to 16 records); larger candidate sets take greedy_u8.
 constexpr int kRegTiles = 5;
 
-// Rebuild of dirty nodes for uint8 rows of 64*NK bytes with R <= 64 and
-// R + P <= 128 (the same steps as k_rebuild).  When a node prunes, D_u of
-// every candidate comes from int8 MFMA of u's row against the candidates,
-// 16 at a time (exact, so it equals the distances the records carry); the
-// keys are sorted and greedy_u8 selects.  Only a few registers per
-// candidate tile are live at a time, so many waves fit per SIMD to hide
-// the gathers.
+// Rebuild of dirty nodes for uint8 rows of 64*NK bytes with P <= 64.  When a
+// node prunes, its candidates are sorted by (D_u, id) and greedy_u8_reg (or
+// greedy_u8, for more than 80 of them) selects.
 template <int NK>
 __global__ __launch_bounds__(64, 4) void k_rebuild_mr(RebuildArgs a) {
   constexpr int NC = 2;
   __shared__ uint4 rowL[16];
   __shared__ uint32_t cl[64 * NC];
-  __shared__ float cdL[64 * NC];  // D_u of the candidates, from the stored list distances
+  __shared__ float cdL[64 * NC];  // D_u of the candidates
   __shared__ uint32_t spos[64 * NC];
   __shared__ float dpos[64 * NC];
   __shared__ int thrL[64 * NC];
   __shared__ int nrmL[64 * NC];
   __shared__ uint32_t oid[64];
   __shared__ float od[64];
-  const int ln = lane(), g = ln >> 4, col = ln & 15;
+  const int ln = lane();
   const PoolView &P = a.pool;
   const uint32_t R = P.R;
   const uint32_t nd_total = *a.list_n;
-  const size_t goff = (size_t)g * 16;
   unsigned long long evals = 0;
   uint32_t prunes = 0, nodes = 0, recs = 0, cand = 0;
   // the next node of this wave is read while the current one is rebuilt
@@ -1019,64 +399,15 @@ __global__ __launch_bounds__(64, 4) void k_rebuild_mr(RebuildArgs a) {
     u_next = a.list[it + gridDim.x < nd_total ? it + gridDim.x : it];
     nodes++;
     uint32_t nrec;
-    const int m = collect_candidates<1>(a, u, rowL, cl, nrec, P.adjd ? cdL : nullptr);
+    const int m = collect_candidates<1>(a, u, rowL, cl, nrec, cdL);
     recs += nrec;
     if (m <= (int)R) {
       if (ln < (int)R) P.adj[(size_t)u * R + ln] = ln < m ? cl[ln] : kInvalid;
-      if (P.adjd && ln < (int)R) P.adjd[(size_t)u * R + ln] = ln < m ? cdL[ln] : 0.0f;
+      if (ln < (int)R) P.adjd[(size_t)u * R + ln] = ln < m ? cdL[ln] : 0.0f;
       if (ln == 0) P.deg[u] = (uint32_t)m;
       __syncthreads();
       continue;
     }
-    // D_u of every candidate (list order), into dpos: stored, or by int8
-    // MFMA of u's row against the candidates
-    if (P.adjd) {
-#pragma unroll
-      for (int r = 0; r < NC; r++)
-        if (r * 64 + ln < m) dpos[r * 64 + ln] = cdL[r * 64 + ln];
-    } else {
-      v4i A[NK];
-      int np = 0;
-      const uint8_t *urow = P.vecs + (size_t)u * P.stride + goff;
-#pragma unroll
-      for (int kk = 0; kk < NK; kk++) {
-        A[kk] = to_i8x16(ld16(urow + (size_t)kk * 64));
-        np = sq_i8x16(A[kk], np);
-      }
-      np += (int)xshfl((uint32_t)np, 16);
-      np += (int)xshfl((uint32_t)np, 32);
-      // candidate tiles kRegTiles at a time (one batch when |C| <= 80), all
-      // loads of a batch issued before the first is used
-      for (int t0 = 0; 16 * t0 < m; t0 += kRegTiles) {
-        uint4 raw[kRegTiles][NK];
-#pragma unroll
-        for (int h = 0; h < kRegTiles; h++) {
-          const int e = 16 * (t0 + h) + col;
-#pragma unroll
-          for (int kk = 0; kk < NK; kk++)
-            raw[h][kk] = e - col < m ? ld16(P.vecs + (size_t)(e < m ? cl[e] : u) * P.stride + goff + (size_t)kk * 64)
-                                     : make_uint4(0, 0, 0, 0);
-        }
-#pragma unroll
-        for (int h = 0; h < kRegTiles; h++) {
-          const int e = 16 * (t0 + h) + col;
-          if (e - col >= m) break;
-          int sq = 0;
-          v4i acc = {0, 0, 0, 0};
-#pragma unroll
-          for (int kk = 0; kk < NK; kk++) {
-            const v4i b = to_i8x16(raw[h][kk]);
-            sq = sq_i8x16(b, sq);
-            acc = mfma_i8(A[kk], b, acc);
-          }
-          sq += (int)xshfl((uint32_t)sq, 16);
-          sq += (int)xshfl((uint32_t)sq, 32);
-          if (g == 0) dpos[e] = canon0((float)(np + sq - 2 * acc[0]));
-        }
-      }
-    }
-    if (!P.adjd) evals += (unsigned long long)m;
-    __syncthreads();
     // Candidates by (D_u, id): 32-bit keys D << 7 | list position (uint8
     // distances are integers below 2^23) order them when no two share a
     // distance; a tie, which the id decides, takes the 64-bit key sort.
@@ -1084,7 +415,7 @@ __global__ __launch_bounds__(64, 4) void k_rebuild_mr(RebuildArgs a) {
 #pragma unroll
     for (int r = 0; r < NC; r++) {
       const int e = r * 64 + ln;
-      k32[r] = e < m ? ((uint32_t)dpos[e] << 7) | (uint32_t)e : ~0u;
+      k32[r] = e < m ? ((uint32_t)cdL[e] << 7) | (uint32_t)e : ~0u;
     }
     wave_sort32<NC>(k32);
     bool tie = false;
@@ -1109,9 +440,8 @@ __global__ __launch_bounds__(64, 4) void k_rebuild_mr(RebuildArgs a) {
 #pragma unroll
       for (int r = 0; r < NC; r++) {
         const int e = r * 64 + ln;
-        key[r] = e < m ? key64(dpos[e], cl[e]) : ~0ull;
+        key[r] = e < m ? key64(cdL[e], cl[e]) : ~0ull;
       }
-      __syncthreads();
       wave_sort64<NC>(key);
 #pragma unroll
       for (int r = 0; r < NC; r++) {
@@ -1139,10 +469,10 @@ __global__ __launch_bounds__(64, 4) void k_rebuild_mr(RebuildArgs a) {
       __syncthreads();
     }
     if (ln < (int)R) P.adj[(size_t)u * R + ln] = ln < nsel ? oid[ln] : kInvalid;
-    if (P.adjd && ln < (int)R) P.adjd[(size_t)u * R + ln] = ln < nsel ? od[ln] : 0.0f;
+    if (ln < (int)R) P.adjd[(size_t)u * R + ln] = ln < nsel ? od[ln] : 0.0f;
     if (ln == 0) P.deg[u] = (uint32_t)nsel;
     prunes++;
-    cand += (unsigned long long)m + (P.adjd ? 0u : 1u);
+    cand += (unsigned long long)m;
     __syncthreads();
   }
   if (ln == 0) {
@@ -1168,7 +498,7 @@ __global__ __launch_bounds__(64) void k_rebuild_fast(RebuildArgs a) {
   __shared__ uint4 rowL[64];
   __shared__ uint32_t srcL[64];
   __shared__ uint32_t outL[4 * 64];
-  __shared__ float outD[4 * 64];  // stored list distances, when the pool keeps them
+  __shared__ float outD[4 * 64];  // their list distances
   const int ln = lane(), s = ln >> 4, q = ln & 15;
   const PoolView &P = a.pool;
   const uint32_t R = P.R, R4 = R >> 2;
@@ -1187,7 +517,7 @@ __global__ __launch_bounds__(64) void k_rebuild_fast(RebuildArgs a) {
       g1 = a.goff[u + 1];
       if ((uint32_t)q < R4) {
         rw = *reinterpret_cast<const uint4 *>(P.adj + (size_t)u * R + 4 * q);
-        if (P.adjd) rd = *reinterpret_cast<const float4 *>(P.adjd + (size_t)u * R + 4 * q);
+        rd = *reinterpret_cast<const float4 *>(P.adjd + (size_t)u * R + 4 * q);
       }
     }
     const uint32_t nrec = g1 - g0;
@@ -1251,14 +581,12 @@ __global__ __launch_bounds__(64) void k_rebuild_fast(RebuildArgs a) {
       o.z = e + 2 < m ? outL[s * 64 + e + 2] : kInvalid;
       o.w = e + 3 < m ? outL[s * 64 + e + 3] : kInvalid;
       *reinterpret_cast<uint4 *>(P.adj + (size_t)u * R + e) = o;
-      if (P.adjd) {
-        float4 d;
-        d.x = e + 0 < m ? outD[s * 64 + e + 0] : 0.0f;
-        d.y = e + 1 < m ? outD[s * 64 + e + 1] : 0.0f;
-        d.z = e + 2 < m ? outD[s * 64 + e + 2] : 0.0f;
-        d.w = e + 3 < m ? outD[s * 64 + e + 3] : 0.0f;
-        *reinterpret_cast<float4 *>(P.adjd + (size_t)u * R + e) = d;
-      }
+      float4 d;
+      d.x = e + 0 < m ? outD[s * 64 + e + 0] : 0.0f;
+      d.y = e + 1 < m ? outD[s * 64 + e + 1] : 0.0f;
+      d.z = e + 2 < m ? outD[s * 64 + e + 2] : 0.0f;
+      d.w = e + 3 < m ? outD[s * 64 + e + 3] : 0.0f;
+      *reinterpret_cast<float4 *>(P.adjd + (size_t)u * R + e) = d;
     }
     if (install && q == 0) P.deg[u] = (uint32_t)m;
     // nodes left for the general kernel are flagged by list position and
@@ -1284,11 +612,10 @@ __global__ __launch_bounds__(64) void k_rebuild_fast(RebuildArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// fp32 rebuild of queued dirty nodes (R <= 64, P <= 64 * NP), one wave per
-// node, persistent over twice the resident workgroups: C and its distances as
-// in k_rebuild_mr (stored list distances, records), a 64-bit-key sort, then
-// prune_gram.
-template <int NP>
+// Rebuild of queued dirty nodes for rows of any length (P <= 64 * NP), one
+// wave per node, persistent over twice the resident workgroups: C and its
+// distances as in k_rebuild_mr, a 64-bit-key sort, then prune_gram.
+template <int KIND, int NP>
 __global__ __launch_bounds__(64, 3) void k_rebuild_gram(RebuildArgs a) {
   constexpr int NC = NP == 1 ? 2 : 4;  // 64 + 64 * NP candidates at most, in a power of two of rows
   __shared__ uint4 rowL[16];
@@ -1325,7 +652,7 @@ __global__ __launch_bounds__(64, 3) void k_rebuild_gram(RebuildArgs a) {
         cdL[r * 64 + ln] = unsortable((uint32_t)(key[r] >> 32));
       }
       __syncthreads();
-      n = prune_gram<NC>(P, u, m, R, a.coef, cl, cdL, oid, od, ntile);
+      n = prune_gram<KIND, NC>(P, u, m, R, a.coef, cl, cdL, oid, od, ntile);
       ids = oid;
       ds = od;
       prunes++;
@@ -1349,9 +676,9 @@ __global__ __launch_bounds__(64, 3) void k_rebuild_gram(RebuildArgs a) {
   }
 }
 
-// Forward GrANDRobustPrune of new fp32 points: V_i with the search's D, a
-// 64-bit-key sort, then prune_gram.
-template <int NR>
+// Forward GrANDRobustPrune of new points with rows of any length: V_i with the
+// search's D, a 64-bit-key sort, then prune_gram.
+template <int KIND, int NR>
 __global__ __launch_bounds__(64, 3) void k_fwd_prune_gram(FwdPruneArgs a) {
   __shared__ uint32_t spos[64 * (NR < 2 ? 2 : NR)];
   __shared__ __align__(16) float dpos[64 * (NR < 2 ? 2 : NR)];
@@ -1383,7 +710,7 @@ __global__ __launch_bounds__(64, 3) void k_fwd_prune_gram(FwdPruneArgs a) {
   }
   __syncthreads();
   uint32_t ntile = 0;
-  const int nsel = prune_gram<NR>(P, p, m, R, a.coef, spos, dpos, oid, od, ntile);
+  const int nsel = prune_gram<KIND, NR>(P, p, m, R, a.coef, spos, dpos, oid, od, ntile);
   if (ln < (int)R) {
     const bool in = ln < nsel;
     const uint32_t sid = in ? oid[ln] : kInvalid;
@@ -1402,80 +729,15 @@ __global__ __launch_bounds__(64, 3) void k_fwd_prune_gram(FwdPruneArgs a) {
   }
 }
 
-// LDS bytes for staging `rows` candidate rows plus the node's own row.
-static size_t staged_bytes(size_t stride, uint32_t rows) { return (size_t)(rows + 1) * lds_stride(stride); }
-constexpr size_t kMaxStagedLds = 16 * 1024;  // larger footprints limit occupancy more than staging saves
-
-// The matrix-core prune applies to uint8 rows whose chunk count is a
-// multiple of 4 (dim a multiple of 64), i.e. whole 64-byte MFMA K steps.
-static bool mfma_ok(int kind, const PoolView &P) { return kind == kU8L2 && P.nch % 4 == 0; }
-
-hipError_t launch_fwd_prune(int kind, int vc, uint32_t max_iters, const FwdPruneArgs &a, hipStream_t st) {
+hipError_t launch_fwd_prune(int kind, uint32_t max_iters, const FwdPruneArgs &a, hipStream_t st) {
   if (a.n == 0) return hipSuccess;
-  if (kind == kU8L2 && a.pool.R <= 64 && (a.pool.nch == 8 || a.pool.nch == 4)) {
-    GR_DISPATCH_N(max_iters, {
-      if (a.pool.nch == 8) hipLaunchKernelGGL((k_fwd_prune_mr<2, NR>), dim3(a.n), dim3(64), 0, st, a);
-      else hipLaunchKernelGGL((k_fwd_prune_mr<1, NR>), dim3(a.n), dim3(64), 0, st, a);
-      return hipGetLastError();
-    });
-  }
-  if (kind == kF32L2) {
-    GR_DISPATCH_N(max_iters, {
-      hipLaunchKernelGGL((k_fwd_prune_gram<NR>), dim3(a.n), dim3(64), 0, st, a);
-      return hipGetLastError();
-    });
-  }
-  if (kind != kU8L2) return hipErrorInvalidValue;  // Vamana lists are pruned by L2 distances
-  GR_DISPATCH_VC_U8(vc, GR_DISPATCH_N(max_iters, {
-    const size_t lds = staged_bytes(a.pool.stride, 64 * NR);
-    const size_t mlds = mfma_lds_bytes(a.pool.stride, 64 * NR);
-    if (mfma_ok(kind, a.pool) && mlds <= kMaxStagedLds) {
-      hipLaunchKernelGGL((k_fwd_prune<KIND, LPV, CPL, NR, kMfma>), dim3(a.n), dim3(64), mlds, st, a);
-      return hipGetLastError();
-    }
-    if (lds <= kMaxStagedLds) {
-      hipLaunchKernelGGL((k_fwd_prune<KIND, LPV, CPL, NR, kStaged>), dim3(a.n), dim3(64), lds, st, a);
-    } else {
-      hipLaunchKernelGGL((k_fwd_prune<KIND, LPV, CPL, NR, kGlobal>), dim3(a.n), dim3(64), 0, st, a);
-    }
+  if (a.pool.R > 64 || (kind != kU8L2 && kind != kF32L2)) return hipErrorInvalidValue;
+  GR_DISPATCH_N(max_iters, {
+    if (kind == kU8L2) hipLaunchKernelGGL((k_fwd_prune_gram<kU8L2, NR>), dim3(a.n), dim3(64), 0, st, a);
+    else hipLaunchKernelGGL((k_fwd_prune_gram<kF32L2, NR>), dim3(a.n), dim3(64), 0, st, a);
     return hipGetLastError();
-  }));
+  });
   return hipErrorInvalidValue;
-}
-
-
-template <int KIND, int LPV, int CPL, int NP, int NC>
-static void launch_rebuild_t(const RebuildArgs &a, uint32_t grid, hipStream_t st) {
-  const size_t lds = staged_bytes(a.pool.stride, 64 * NC);
-  const size_t mlds = mfma_lds_bytes(a.pool.stride, 64 * NC);
-  if constexpr (NC == 2 && NP == 1) {
-    // persistent waves, twice the resident workgroups: the second half
-    // starts as the first ones finish, which evens out the work per wave
-    if (a.pool.R <= 64 && a.pool.nch == 8) {
-      static const uint32_t res = resident_blocks((const void *)k_rebuild_mr<2>);
-      hipLaunchKernelGGL(k_rebuild_mr<2>, dim3(clamp_resident(grid, 2 * res)), dim3(64), 0, st, a);
-      return;
-    }
-    if (a.pool.R <= 64 && a.pool.nch == 4) {
-      static const uint32_t res = resident_blocks((const void *)k_rebuild_mr<1>);
-      hipLaunchKernelGGL(k_rebuild_mr<1>, dim3(clamp_resident(grid, 2 * res)), dim3(64), 0, st, a);
-      return;
-    }
-  }
-  if (mfma_ok(KIND, a.pool) && mlds <= kMaxStagedLds) {
-    hipLaunchKernelGGL((k_rebuild<KIND, LPV, CPL, NP, NC, kMfma>), dim3(grid), dim3(64), mlds, st, a);
-    return;
-  }
-  if (lds <= kMaxStagedLds) {
-    hipLaunchKernelGGL((k_rebuild<KIND, LPV, CPL, NP, NC, kStaged>), dim3(grid), dim3(64), lds, st, a);
-  } else {
-    hipLaunchKernelGGL((k_rebuild<KIND, LPV, CPL, NP, NC, kGlobal>), dim3(grid), dim3(64), 0, st, a);
-  }
-}
-
-bool adj_dists_apply(int kind, uint32_t R, int nch, uint32_t P) {
-  if (kind == kF32L2) return true;
-  return kind == kU8L2 && R <= 64 && R % 4 == 0 && (nch == 8 || nch == 4) && P <= 64 && R + P <= 128;
 }
 
 // One wave per row, lane s for list entry s: the squared distance of u and
@@ -1519,18 +781,26 @@ hipError_t launch_adj_dists(PoolView p, int kind, hipStream_t s) {
   return hipGetLastError();
 }
 
+// One persistent rebuild kernel over the queue: twice the resident
+// workgroups, so that the second half starts as the first ones finish, which
+// evens out the work per wave.
+#define GR_REBUILD(...)                                                                                 \
+  do {                                                                                                  \
+    static const uint32_t res = resident_blocks((const void *)__VA_ARGS__);                             \
+    hipLaunchKernelGGL((__VA_ARGS__), dim3(clamp_resident(grid, 2 * res)), dim3(64), 0, st, a);         \
+  } while (0)
+
 // Dirty nodes are rebuilt by the fast kernel when the row layout allows it
-// (R <= 64, R a multiple of 4); the nodes it leaves, and every node
-// otherwise, by the general kernel of the configuration.
-hipError_t launch_rebuild(int kind, int vc, uint32_t R, uint32_t P, const RebuildArgs &a0, uint32_t grid,
-                          hipStream_t st) {
+// (R a multiple of 4); the nodes it leaves, and every node otherwise, by the
+// pruning kernel of the configuration.
+hipError_t launch_rebuild(int kind, uint32_t R, uint32_t P, const RebuildArgs &a0, uint32_t grid, hipStream_t st) {
   if (grid == 0) return hipSuccess;
-  if (P > 128 || R + P > 256) return hipErrorInvalidValue;
+  if (P > 128 || R > 64 || (kind != kU8L2 && kind != kF32L2)) return hipErrorInvalidValue;
   RebuildArgs a = a0;
   a.list = a0.dirty;
   a.list_n = &a0.ds->n_dirty;
   a.count_nodes = 1;
-  if (R <= 64 && R % 4 == 0) {
+  if (R % 4 == 0) {
     // grid >= min(records, 8192) >= the blocks needed at four nodes per wave
     hipLaunchKernelGGL(k_rebuild_fast, dim3(grid), dim3(64), 0, st, a);
     hipError_t e = launch_compact_flags(a.qflag, a.list, a.list_n, a0.flag_cap, a.queue, a.queue_n, a.scan_tmp, st);
@@ -1539,25 +809,20 @@ hipError_t launch_rebuild(int kind, int vc, uint32_t R, uint32_t P, const Rebuil
     a.list_n = a0.queue_n;
     a.count_nodes = 0;
   }
-  if (kind == kF32L2) {
-    static const uint32_t r1 = resident_blocks((const void *)k_rebuild_gram<1>);
-    static const uint32_t r2 = resident_blocks((const void *)k_rebuild_gram<2>);
-    if (P <= 64) hipLaunchKernelGGL(k_rebuild_gram<1>, dim3(clamp_resident(grid, 2 * r1)), dim3(64), 0, st, a);
-    else hipLaunchKernelGGL(k_rebuild_gram<2>, dim3(clamp_resident(grid, 2 * r2)), dim3(64), 0, st, a);
-    return hipGetLastError();
+  // uint8 rows of 64 and 128 bytes: a node's tiles stay in registers and only
+  // the tiles that still hold a live candidate are multiplied (0.42 ms per
+  // launch of a 10,000-point batch on 1M x 128, prune_gram 0.54)
+  if (kind == kU8L2 && P <= 64 && (a.pool.nch == 8 || a.pool.nch == 4)) {
+    if (a.pool.nch == 8) GR_REBUILD(k_rebuild_mr<2>);
+    else GR_REBUILD(k_rebuild_mr<1>);
+  } else if (kind == kU8L2) {
+    if (P <= 64) GR_REBUILD(k_rebuild_gram<kU8L2, 1>);
+    else GR_REBUILD(k_rebuild_gram<kU8L2, 2>);
+  } else {
+    if (P <= 64) GR_REBUILD(k_rebuild_gram<kF32L2, 1>);
+    else GR_REBUILD(k_rebuild_gram<kF32L2, 2>);
   }
-  if (kind != kU8L2) return hipErrorInvalidValue;
-  GR_DISPATCH_VC_U8(vc, {
-    if (P <= 64 && R + P <= 128) {
-      launch_rebuild_t<KIND, LPV, CPL, 1, 2>(a, grid, st);
-    } else if (P <= 64) {
-      launch_rebuild_t<KIND, LPV, CPL, 1, 4>(a, grid, st);
-    } else {
-      launch_rebuild_t<KIND, LPV, CPL, 2, 4>(a, grid, st);
-    }
-    return hipGetLastError();
-  });
-  return hipErrorInvalidValue;
+  return hipGetLastError();
 }
 
 }  // namespace gr

@@ -103,10 +103,10 @@ __device__ __forceinline__ void search_one(SearchArgs a) {
   const uint32_t qi = blockIdx.x;
   if (qi >= a.nq) return;
   const PoolView &P = a.pool;
-  const uint8_t *qrow = a.qids ? P.vecs + (size_t)a.qids[qi] * P.stride : a.qbase + (size_t)qi * P.stride;
+  const uint8_t *qrow = a.qids ? P.vecs + (size_t)a.qids[qi] * P.stride : a.qbase + (size_t)qi * a.q_stride;
   const uint32_t start = a.start_ptr ? *a.start_ptr : a.start;
   Slice<KIND, LPV, CPL> s;
-  load_slice<KIND, LPV, CPL>(s, qrow, P.nch);
+  load_slice<KIND, LPV, CPL>(s, qrow, a.qids ? P.nch : a.q_nch);
   uint32_t *vrow = EXACT ? a.vis + (size_t)qi * a.vis_words : nullptr;
   if (!EXACT)
     for (int i = ln; i < kSlots; i += 64) hsh[i] = H::kEmpty;
