@@ -125,16 +125,13 @@ __device__ __forceinline__ int kill_threshold(double coef, double inv, float D) 
 }
 
 // Dist of two pool rows (squared L2), by the whole wave: lane l adds chunks
-// l, l + 64, ... in fp64.  The rounded result is that of the sum in dimension
-// order: where the two orders (they differ by less than 2^-40 of the sum for
-// rows of up to 1024 floats) could round apart, that sum is taken instead.
+// l, l + 64, ... in fp64.  The result is that of the sum in dimension order.
 __device__ __forceinline__ float pair_l2(const PoolView &P, uint32_t a, uint32_t b) {
   const uint8_t *ra = P.vecs + (size_t)a * P.stride, *rb = P.vecs + (size_t)b * P.stride;
   double s = 0.0;
   for (int c = lane(); c < P.nch; c += 64) s = l2_4(ld16(ra + (size_t)c * 16), ld16(rb + (size_t)c * 16), s);
   s = group_sum<64>(s);
-  const float f0 = (float)(s * (1.0 - 0x1p-40)), f1 = (float)(s * (1.0 + 0x1p-40));
-  if (f0 != f1) {
+  if (!rounds_once(s, s * 0x1p-42)) {
     s = 0.0;
     for (int c = 0; c < P.nch; c++) s = l2_4(ld16(ra + (size_t)c * 16), ld16(rb + (size_t)c * 16), s);
   }

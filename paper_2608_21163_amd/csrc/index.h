@@ -53,7 +53,7 @@ struct DevScalars {
                                     // uint8 data: low 64 bits of the exact integer key)
   unsigned long long best_hi;       // uint8 medoid search: high 64 bits of the smallest key
   uint32_t need_medoid;             // medoid kernels run only when set
-  uint32_t pad_;
+  uint32_t n_prop;                  // CAGRA construction: proposals of a join launch
   unsigned long long n_count;       // scratch counter (active ids at import)
   unsigned long long stat[kStatSlots * kStatWords];
 };
@@ -191,10 +191,10 @@ struct BuildArgs {
   float *nd;
   uint32_t *ns, *os;          // n x S new and old samples
   uint32_t *cand, *cnb;       // n x 4S join candidates (Bn, then Bo) and nb | no << 16
-  uint32_t *pcnt;             // proposals per node
-  const uint32_t *poff;       // their exclusive scan (n + 1)
-  uint32_t v0, v1;            // nodes of one join chunk
-  int stage_rows;             // join: candidate rows staged in dynamic LDS
+  uint32_t v0, v1;            // nodes of one join launch
+  uint32_t *pcnt;             // per node: its join blocks that found no room
+  int retry;                  // join: only those blocks
+  size_t rcap;                // records the buffers hold
   uint32_t *rec_t, *rec_s;    // records (target, source, key)
   float *rec_d;
   const uint32_t *goff, *gsrc;  // grouped records (offsets per target, sources, keys)
@@ -208,7 +208,7 @@ hipError_t launch_build_check(const BuildArgs &a, hipStream_t s);
 hipError_t launch_build_init(int kind, const BuildArgs &a, hipStream_t s);
 hipError_t launch_build_sample(const BuildArgs &a, hipStream_t s);
 hipError_t launch_build_cands(const BuildArgs &a, hipStream_t s);
-hipError_t launch_build_join(int kind, const BuildArgs &a, bool write, hipStream_t s);
+hipError_t launch_build_join(int kind, const BuildArgs &a, hipStream_t s);
 hipError_t launch_build_merge(const BuildArgs &a, uint32_t grid, hipStream_t s);
 hipError_t launch_build_rank(const BuildArgs &a, hipStream_t s);
 hipError_t launch_build_out(const BuildArgs &a, hipStream_t s);

@@ -54,6 +54,12 @@ template <> struct Acc<kU8L2> { typedef uint32_t T; };
 template <> struct Acc<kF32L2> { typedef double T; };
 template <> struct Acc<kF32IP> { typedef double T; };
 
+// Whether a sum s known to e rounds to fp32 in one way only.  Two orders of a
+// sum of at most 1024 fp64 terms differ by less than 2^-42 of the sum of the
+// terms' magnitudes; a kernel that needs the value of the sum in dimension
+// order, and adds in another, sums again where this is false.
+__device__ __forceinline__ bool rounds_once(double s, double e) { return (float)(s - e) == (float)(s + e); }
+
 template <int KIND, int LPV, int CPL>
 struct Slice {
   uint4 q[CPL];

@@ -480,6 +480,34 @@ __device__ __forceinline__ void wave_sort64(uint64_t (&k)[N]) {
   }
 }
 
+// Bitonic merge (input bitonic) of N*64 64-bit keys to ascending order.
+template <int N>
+__device__ __forceinline__ void wave_merge_up64(uint64_t (&k)[N]) {
+  const int ln = lane();
+#pragma unroll
+  for (int j = 32 * N; j > 0; j >>= 1) {
+    if (j >= 64) {
+      const int jr = j >> 6;
+#pragma unroll
+      for (int r = 0; r < N; r++) {
+        const int p = r ^ jr;
+        if (p > r) {
+          const uint64_t a = k[r], b = k[p];
+          const bool sw = b < a;
+          k[r] = sw ? b : a;
+          k[p] = sw ? a : b;
+        }
+      }
+    } else {
+#pragma unroll
+      for (int r = 0; r < N; r++) {
+        const uint64_t o = xshfl64(k[r], j);
+        k[r] = ((o < k[r]) == ((ln & j) == 0)) ? o : k[r];
+      }
+    }
+  }
+}
+
 // Bitonic sort, ascending, of N*64 32-bit keys held as element e = r*64 + lane.
 template <int N>
 __device__ __forceinline__ void wave_sort32(uint32_t (&k)[N]) {
