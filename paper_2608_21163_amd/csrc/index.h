@@ -67,7 +67,7 @@ enum { kErrRange = 1, kErrRepeat = 2, kErrState = 3, kErrNonFinite = 4, kErrNorm
 
 // Vector-layout classes: lanes per row (LPV) and 16-byte chunks per lane
 // (CPL) of the distance machinery, chosen from the padded row length.
-enum { kVcA = 0, kVcB = 1, kVcC = 2 };  // <= 8 chunks, <= 32 chunks, <= 256 chunks
+enum { kVcA = 0, kVcB, kVcC, kVcD, kVcE };  // <= 8, 32, 64, 128 and 256 chunks
 
 // Pool view passed to kernels.
 struct PoolView {

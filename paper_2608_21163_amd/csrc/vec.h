@@ -127,6 +127,40 @@ __device__ __forceinline__ typename Acc<KIND>::T partial(const Slice<KIND, LPV, 
   return acc;
 }
 
+template <int KIND, int LPV, int CPL>
+__device__ __forceinline__ void partial2(const Slice<KIND, LPV, CPL>& s, const uint4 (&a)[CPL], const uint4 (&b)[CPL],
+                                         typename Acc<KIND>::T& ta, typename Acc<KIND>::T& tb) {
+  if (KIND == kU8L2) ta = tb = s.qn;
+#pragma unroll
+  for (int k = 0; k < CPL; k++) {
+    if constexpr (KIND == kU8L2) {
+      ta = u8l2_4(s.q[k], a[k], ta);
+      tb = u8l2_4(s.q[k], b[k], tb);
+    } else {
+      const float *q = reinterpret_cast<const float *>(&s.q[k]), *fa = reinterpret_cast<const float *>(&a[k]),
+                  *fb = reinterpret_cast<const float *>(&b[k]);
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        const double x = (double)q[i];
+        if constexpr (KIND == kF32L2) {
+          const double da = (double)fa[i] - x, db = (double)fb[i] - x;
+          ta = __builtin_fma(da, da, ta);
+          tb = __builtin_fma(db, db, tb);
+        } else {
+          ta = __builtin_fma(x, (double)fa[i], ta);
+          tb = __builtin_fma(x, (double)fb[i], tb);
+        }
+      }
+    }
+  }
+}
+
+__device__ __forceinline__ uint32_t xshfl_any(uint32_t v, int j) { return xshfl(v, j); }
+__device__ __forceinline__ double xshfl_any(double v, int j) {
+  const uint64_t b = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = xshfl((uint32_t)b, j), hi = xshfl((uint32_t)(b >> 32), j);
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
 template <int LPV>
 __device__ __forceinline__ uint32_t group_sum(uint32_t v) {
 #pragma unroll
@@ -136,12 +170,35 @@ __device__ __forceinline__ uint32_t group_sum(uint32_t v) {
 template <int LPV>
 __device__ __forceinline__ double group_sum(double v) {
 #pragma unroll
-  for (int o = 1; o < LPV; o <<= 1) {
-    const uint64_t b = (uint64_t)__double_as_longlong(v);
-    const uint32_t lo = xshfl((uint32_t)b, o), hi = xshfl((uint32_t)(b >> 32), o);
-    v += __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
-  }
+  for (int o = 1; o < LPV; o <<= 1) v += xshfl_any(v, o);
   return v;
+}
+
+// The sums over each group of W lanes of N values (N a power of two below W):
+// at every step the lower half of a group passes on one value and the upper
+// half the other, so N values cost N - 1 + log2(W / N) exchanges instead of
+// N * log2(W).  Returned: in lane l the sum of value fold_index<N, W>().
+template <int N, int W, class T>
+__device__ __forceinline__ T fold_sum(T (&t)[N]) {
+  if constexpr (N == 1) {
+    return group_sum<W>(t[0]);
+  } else {
+    const bool up = (lane() & (W / 2)) != 0;
+    T h[N / 2];
+#pragma unroll
+    for (int i = 0; i < N / 2; i++) {
+      const T keep = up ? t[i + N / 2] : t[i], pass = up ? t[i] : t[i + N / 2];
+      h[i] = keep + xshfl_any(pass, W / 2);
+    }
+    return fold_sum<N / 2, W / 2>(h);
+  }
+}
+template <int N, int W>
+__device__ __forceinline__ int fold_index() {
+  int r = 0;
+#pragma unroll
+  for (int n = N, w = W; n > 1; n >>= 1, w >>= 1) r += (lane() & (w / 2)) ? n / 2 : 0;
+  return r;
 }
 
 template <int KIND>
@@ -153,34 +210,82 @@ __device__ __forceinline__ float finalize(typename Acc<KIND>::T t) {
 
 // Distances from the slice to rows ids[0..cnt) (ids in LDS), written to
 // out[0..cnt) (LDS).  All gathers of RIF steps are issued before any is
-// consumed so that many rows are in flight per wave.
+// consumed so that many rows are in flight per wave: 8 chunks per lane for
+// rows of 8 lanes (64 rows of one chunk a lane, 16 rows of four), 32 for
+// longer rows, whose few sums are folded (fold_sum), and one row's 16 chunks
+// per lane for the longest rows of a wave that has its SIMD to itself.
 template <int KIND, int LPV, int CPL>
 __device__ __forceinline__ void wave_dists(const Slice<KIND, LPV, CPL>& s, const uint8_t* __restrict__ vecs,
                                            size_t stride, int nch, const uint32_t* ids, float* out, int cnt) {
   constexpr int G = 64 / LPV;
-  constexpr int RIF = CPL >= 8 ? 1 : 8 / CPL;
+  constexpr bool kFold = LPV >= 16 && CPL <= 4;
+  constexpr int RIF = kFold ? 32 / CPL : CPL >= 8 ? 1 : 8 / CPL;
   const int ln = lane(), grp = ln / LPV, sub = ln % LPV;
   for (int base = 0; base < cnt; base += G * RIF) {
     // steps whose rows all lie beyond cnt are skipped (uniform branches)
     const int steps = (cnt - base + G - 1) / G;
     uint4 b[RIF][CPL];
+    if constexpr (kFold) {
+      // The ids are read together (a read per step waits for LDS before each
+      // step's gathers), groups past the rows gather the last one again, and
+      // lanes past a row's chunks its last one, cleared afterwards (a branch
+      // around each load took ten instructions of a wave that has its SIMD to
+      // itself; the first two chunks of a lane always exist).
+      uint32_t rid[RIF], off[CPL], mask[CPL];
 #pragma unroll
-    for (int rr = 0; rr < RIF; rr++) {
-      if (rr >= steps) break;
-      const int c = base + rr * G + grp;
-      const uint8_t* row = vecs + (size_t)(c < cnt ? ids[c] : 0u) * stride;
+      for (int rr = 0; rr < RIF; rr++) rid[rr] = ids[min(base + rr * G + grp, cnt - 1)];
 #pragma unroll
       for (int k = 0; k < CPL; k++) {
         const int ch = sub + k * LPV;
-        b[rr][k] = (rr < steps && c < cnt && ch < nch) ? ld16(row + (size_t)ch * 16) : make_uint4(0, 0, 0, 0);
+        off[k] = (uint32_t)min(ch, nch - 1) * 16u;
+        mask[k] = ch < nch ? ~0u : 0u;
       }
-    }
 #pragma unroll
-    for (int rr = 0; rr < RIF; rr++) {
-      if (rr >= steps) break;
-      const int c = base + rr * G + grp;
-      typename Acc<KIND>::T t = group_sum<LPV>(partial<KIND, LPV, CPL>(s, b[rr]));
-      if (sub == 0 && c < cnt) out[c] = finalize<KIND>(t);
+      for (int rr = 0; rr < RIF; rr++) {
+        if ((rr & ~1) >= steps) break;  // whole pairs, as they are summed below
+        const uint32_t id = LPV == 64 ? rdlane(rid[rr], 0) : rid[rr];
+        const uint8_t* row = vecs + (size_t)id * stride;
+#pragma unroll
+        for (int k = 0; k < CPL; k++) b[rr][k] = ld16(row + off[k]);
+      }
+      typename Acc<KIND>::T t[RIF];
+#pragma unroll
+      for (int rr = 0; rr < RIF; rr += 2) {  // two rows' chains of sums beside each other
+        t[rr] = t[rr + 1] = 0;
+        if (rr >= steps) continue;
+#pragma unroll
+        for (int h = 0; h < 2; h++)
+#pragma unroll
+          for (int k = 2; k < CPL; k++) {
+            b[rr + h][k].x &= mask[k];
+            b[rr + h][k].y &= mask[k];
+            b[rr + h][k].z &= mask[k];
+            b[rr + h][k].w &= mask[k];
+          }
+        partial2<KIND, LPV, CPL>(s, b[rr], b[rr + 1], t[rr], t[rr + 1]);
+      }
+      const typename Acc<KIND>::T v = fold_sum<RIF, LPV>(t);
+      const int c = base + fold_index<RIF, LPV>() * G + grp;
+      if (ln % (LPV / RIF) == 0 && c < cnt) out[c] = finalize<KIND>(v);
+    } else {
+#pragma unroll
+      for (int rr = 0; rr < RIF; rr++) {
+        if (rr >= steps) break;
+        const int c = base + rr * G + grp;
+        const uint8_t* row = vecs + (size_t)(c < cnt ? ids[c] : 0u) * stride;
+#pragma unroll
+        for (int k = 0; k < CPL; k++) {
+          const int ch = sub + k * LPV;
+          b[rr][k] = (rr < steps && c < cnt && ch < nch) ? ld16(row + (size_t)ch * 16) : make_uint4(0, 0, 0, 0);
+        }
+      }
+#pragma unroll
+      for (int rr = 0; rr < RIF; rr++) {
+        if (rr >= steps) break;
+        const int c = base + rr * G + grp;
+        typename Acc<KIND>::T t = group_sum<LPV>(partial<KIND, LPV, CPL>(s, b[rr]));
+        if (sub == 0 && c < cnt) out[c] = finalize<KIND>(t);
+      }
     }
   }
 }
