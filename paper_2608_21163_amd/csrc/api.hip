@@ -195,9 +195,9 @@ struct Phase {
 };
 
 // End of every call: wait for the stream, fold timings, refresh the host
-// mirror of the device scalars (medoid, counters).
-grand_status finish(grand_index *h) {
-  HCHK(h, hipMemcpyAsync(h->hs, h->ds, kScalarBytes, hipMemcpyDeviceToHost, h->stream));
+// mirror of the device scalars (medoid, counters; a search changes none).
+grand_status finish(grand_index *h, bool scalars = true) {
+  if (scalars) HCHK(h, hipMemcpyAsync(h->hs, h->ds, kScalarBytes, hipMemcpyDeviceToHost, h->stream));
   HCHK(h, hipStreamSynchronize(h->stream));
   for (auto &t : h->pending) {
     float ms = 0.0f;
@@ -310,14 +310,50 @@ grand_status ensure_query(grand_index *h, uint32_t nq, uint32_t k) {
   return GRAND_OK;
 }
 
-// Whether a copy from p is a copy on the GPU (else p is host memory).
-bool on_device(const void *p) {
+// Whether a copy from p is a copy on a GPU (else p is host memory), and on
+// which one.
+bool on_device(const void *p, int *dev = nullptr) {
   hipPointerAttribute_t a{};
   if (hipPointerGetAttributes(&a, p) != hipSuccess) {
     (void)hipGetLastError();
     return false;
   }
+  if (dev) *dev = a.device;
   return a.type == hipMemoryTypeDevice;
+}
+
+// The buffers a search works in.  Queries of this GPU's memory that need no
+// padding are read, and results there written, where they lie: a copy each way
+// is a launch of about 5 us and a gap after it, which a single query of 95 us
+// sees (the call 132 -> 123 us without its four).  Anything else -- host
+// memory, another GPU's, a misaligned pointer, a result that overlaps another
+// buffer of the call -- goes through the staging buffers.
+struct SearchBuffers {
+  const uint8_t *q;
+  uint32_t *ids;
+  float *dists;
+  bool copy_q, copy_out;
+};
+SearchBuffers search_buffers(int dev, const void *queries, size_t row_bytes, size_t q_stride, uint32_t nq, uint32_t k,
+                             uint32_t *out_ids, float *out_dists, uint8_t *st_q, uint32_t *st_ids, float *st_d) {
+  auto here = [dev](const void *p, size_t align) {
+    int d = -1;
+    return (uintptr_t)p % align == 0 && on_device(p, &d) && d == dev;
+  };
+  auto apart = [](const void *a, size_t na, const void *b, size_t nb) {
+    return (uintptr_t)a + na <= (uintptr_t)b || (uintptr_t)b + nb <= (uintptr_t)a;
+  };
+  const size_t qb = (size_t)nq * row_bytes, ob = (size_t)nq * k * 4;
+  SearchBuffers s;
+  const bool out = here(out_ids, 4) && here(out_dists, 4) && apart(out_ids, ob, out_dists, ob) &&
+                   apart(out_ids, ob, queries, qb) && apart(out_dists, ob, queries, qb);
+  const bool q = q_stride == row_bytes && here(queries, 16);
+  s.copy_q = !q;
+  s.copy_out = !out;
+  s.q = q ? static_cast<const uint8_t *>(queries) : st_q;
+  s.ids = out ? out_ids : st_ids;
+  s.dists = out ? out_dists : st_d;
+  return s;
 }
 
 // Copies n packed rows of row_bytes (host or device memory) to rows of
@@ -1125,26 +1161,26 @@ grand_status grand_search(grand_index *h, const void *queries, uint32_t nq, uint
   if (!queries || !out_ids || !out_dists) return fail(h, GRAND_E_ARG, "null argument");
   HCHK(h, hipSetDevice(h->p.device));
   if ((s = ensure_query(h, nq, k)) != GRAND_OK) return s;
+  const SearchBuffers io = search_buffers(h->p.device, queries, h->row_bytes, h->q_stride, nq, k, out_ids, out_dists,
+                                          h->q_vecs, h->q_ids, h->q_d);
+  if (io.copy_q && (s = stage_rows(h, h->q_vecs, h->q_stride, queries, nq)) != GRAND_OK) return s;
   if (h->p.dtype == GRAND_F32) {
     Phase ph(h, GRAND_PH_VALIDATE);
-    if ((s = stage_rows(h, h->q_vecs, h->q_stride, queries, nq)) != GRAND_OK) return s;
     if ((s = clear_errors(h)) != GRAND_OK) return s;
-    HCHK(h, launch_check_finite(h->q_vecs, nq, h->q_stride, h->p.dim, h->ds, h->stream));
+    HCHK(h, launch_check_finite(io.q, nq, h->q_stride, h->p.dim, h->ds, h->stream));
     if ((s = read_validation(h)) != GRAND_OK) {
       (void)finish(h);
       return s;
     }
-  } else {
-    if ((s = stage_rows(h, h->q_vecs, h->q_stride, queries, nq)) != GRAND_OK) return s;
   }
   if (h->n_active == 0) {
-    HCHK(h, launch_fill_u32(h->q_ids, GRAND_INVALID, (size_t)nq * k, h->stream));
-    HCHK(h, launch_fill_u32(reinterpret_cast<uint32_t *>(h->q_d), 0x7F800000u, (size_t)nq * k, h->stream));
+    HCHK(h, launch_fill_u32(io.ids, GRAND_INVALID, (size_t)nq * k, h->stream));
+    HCHK(h, launch_fill_u32(reinterpret_cast<uint32_t *>(io.dists), 0x7F800000u, (size_t)nq * k, h->stream));
   } else {
     Phase ph(h, GRAND_PH_SEARCH_QUERY);
     SearchArgs a{};
     a.pool = h->pool;
-    a.qbase = h->q_vecs;
+    a.qbase = io.q;
     a.q_stride = h->q_stride;
     a.q_nch = (int)(h->q_stride / 16);
     a.nq = nq;
@@ -1152,17 +1188,19 @@ grand_status grand_search(grand_index *h, const void *queries, uint32_t nq, uint
     a.ell = beam;
     a.max_iters = 2 * beam;
     a.which = 2;
-    a.c_ids = h->q_ids;
-    a.c_d = h->q_d;
+    a.c_ids = io.ids;
+    a.c_d = io.dists;
     a.c_out = k;
     a.ds = h->ds;
     if (grand_status s_ = prep_counting(h, a)) return s_;
     HCHK(h, launch_search(h->kind, h->vc, a, h->stream));
   }
-  HCHK(h, hipMemcpyAsync(out_ids, h->q_ids, (size_t)nq * k * 4, hipMemcpyDefault, h->stream));
-  HCHK(h, hipMemcpyAsync(out_dists, h->q_d, (size_t)nq * k * 4, hipMemcpyDefault, h->stream));
+  if (io.copy_out) {
+    HCHK(h, hipMemcpyAsync(out_ids, h->q_ids, (size_t)nq * k * 4, hipMemcpyDefault, h->stream));
+    HCHK(h, hipMemcpyAsync(out_dists, h->q_d, (size_t)nq * k * 4, hipMemcpyDefault, h->stream));
+  }
   h->st.queried += nq;
-  return finish(h);
+  return finish(h, false);
 }
 
 grand_status grand_search_static(grand_index *h, const void *queries, uint32_t nq, uint32_t k, uint32_t beam,
@@ -1356,17 +1394,20 @@ grand_status grand_reader_search(grand_reader *r, const void *queries, uint32_t 
     r->qcap = nc;
     r->qk = kc;
   }
-  RCHK(r, copy_rows(r->q_vecs, h->q_stride, queries, h->row_bytes, nq, &r->rows, nullptr, 0, r->stream));
+  const SearchBuffers io = search_buffers(h->p.device, queries, h->row_bytes, h->q_stride, nq, k, out_ids, out_dists,
+                                          r->q_vecs, r->q_ids, r->q_d);
+  if (io.copy_q)
+    RCHK(r, copy_rows(r->q_vecs, h->q_stride, queries, h->row_bytes, nq, &r->rows, nullptr, 0, r->stream));
   if (h->p.dtype == GRAND_F32) {
     RCHK(r, launch_fill_u32(&r->ds->err_code, 0u, 2, r->stream));
-    RCHK(r, launch_check_finite(r->q_vecs, nq, h->q_stride, h->p.dim, r->ds, r->stream));
+    RCHK(r, launch_check_finite(io.q, nq, h->q_stride, h->p.dim, r->ds, r->stream));
     RCHK(r, hipMemcpyAsync(r->hs, r->ds, kScalarBytes, hipMemcpyDeviceToHost, r->stream));
     RCHK(r, hipStreamSynchronize(r->stream));
     if (r->hs->err_code) return rfail(r, GRAND_E_ARG, "a query holds a non-finite element");
   }
   SearchArgs a{};
   a.pool = h->pool;
-  a.qbase = r->q_vecs;
+  a.qbase = io.q;
   a.q_stride = h->q_stride;
   a.q_nch = (int)(h->q_stride / 16);
   a.nq = nq;
@@ -1375,13 +1416,15 @@ grand_status grand_reader_search(grand_reader *r, const void *queries, uint32_t 
   a.ell = beam;
   a.max_iters = 2 * beam;
   a.which = 2;
-  a.c_ids = r->q_ids;
-  a.c_d = r->q_d;
+  a.c_ids = io.ids;
+  a.c_d = io.dists;
   a.c_out = k;
   a.ds = r->ds;
   RCHK(r, launch_search(h->kind, h->vc, a, r->stream));
-  RCHK(r, hipMemcpyAsync(out_ids, r->q_ids, (size_t)nq * k * 4, hipMemcpyDefault, r->stream));
-  RCHK(r, hipMemcpyAsync(out_dists, r->q_d, (size_t)nq * k * 4, hipMemcpyDefault, r->stream));
+  if (io.copy_out) {
+    RCHK(r, hipMemcpyAsync(out_ids, r->q_ids, (size_t)nq * k * 4, hipMemcpyDefault, r->stream));
+    RCHK(r, hipMemcpyAsync(out_dists, r->q_d, (size_t)nq * k * 4, hipMemcpyDefault, r->stream));
+  }
   RCHK(r, hipStreamSynchronize(r->stream));
   return GRAND_OK;
 }

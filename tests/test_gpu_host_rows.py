@@ -65,3 +65,44 @@ def test_import_of_several_blocks():
     assert gi.max() > 140_000 and gi.min() < 40_000
     want = ((x[gi].astype(np.float64) - q[:, None].astype(np.float64)) ** 2).sum(-1)
     assert np.allclose(gd, want, rtol=1e-6, atol=0.0)
+
+
+@pytest.mark.parametrize("dtype,dim", [("u8", 128), ("u8", 100), ("f32", 32), ("f32", 30)])
+def test_results_where_they_lie(dtype, dim):
+    """Device buffers of every alignment, and results that overlap another
+    buffer of the call, against host buffers (the staged path)."""
+    import torch
+
+    from paper_2608_21163_amd import GrandIndex
+    from paper_2608_21163_amd.grand import Reader
+
+    say(f"[device results] {dtype} d{dim}")
+    n, nq, k = 600, 40, 10
+    x, q = _points(dtype, n, dim), _points(dtype, n + nq, dim)[n:]
+    g = GrandIndex.from_config(IndexConfig("vamana", dtype, "l2", dim, n, 16, 32), max_batch=n)
+    g.insert(np.arange(n, dtype=np.uint32), x)
+    want = g.search(q, k, 32)
+    r = Reader(g)
+    flat = torch.zeros(nq * dim + 64, dtype=torch.uint8 if dtype == "u8" else torch.float32, device="cuda")
+    for search in (g.search, r.search):
+        for shift in (0, 1, 3, 4, 16):
+            dq = flat[shift:shift + nq * dim].view(nq, dim)
+            dq.copy_(torch.from_numpy(q))
+            ids = torch.full((nq * k + 8,), -1, dtype=torch.int32, device="cuda")
+            d = torch.full((nq * k + 8,), -1.0, device="cuda")
+            search(dq, k, 32, out_ids=ids[shift % 5:shift % 5 + nq * k].view(nq, k),
+                   out_dists=d[shift % 7:shift % 7 + nq * k].view(nq, k))
+            assert np.array_equal(ids[shift % 5:shift % 5 + nq * k].cpu().numpy().view(np.uint32).reshape(nq, k), want[0])
+            assert np.array_equal(d[shift % 7:shift % 7 + nq * k].cpu().numpy().reshape(nq, k), want[1])
+            assert (ids[shift % 5 + nq * k:] == -1).all() and (d[shift % 7 + nq * k:] == -1).all()
+        # ids over the queries themselves, distances beside them
+        buf = torch.zeros(nq * max(dim, 4 * k) * 4, dtype=torch.uint8, device="cuda")
+        dq = buf[:nq * dim * q.itemsize].view(flat.dtype).view(nq, dim)
+        dq.copy_(torch.from_numpy(q))
+        ids = buf[:nq * k * 4].view(torch.int32).view(nq, k)
+        d = torch.zeros(nq, k, device="cuda")
+        search(dq, k, 32, out_ids=ids, out_dists=d)
+        assert np.array_equal(ids.cpu().numpy().view(np.uint32), want[0])
+        assert np.array_equal(d.cpu().numpy(), want[1])
+    r.close()
+    g.close()
