@@ -35,48 +35,6 @@ namespace gr {
 
 constexpr uint32_t kNew = 0x80000000u;  // list entry not yet sampled; reverse records: an old sample
 
-// Dist of two rows of nch 16-byte chunks, one lane, dimensions in order
-// (zero padding adds nothing).
-template <int KIND>
-__device__ __forceinline__ float dist_seq(const uint8_t *a, const uint8_t *b, int nch) {
-  if (KIND == kU8L2) {
-    uint32_t s = 0;
-    for (int c = 0; c < nch; c++) {
-      const uint4 x = ld16(a + 16 * c), y = ld16(b + 16 * c);
-      const uint32_t xw[4] = {x.x, x.y, x.z, x.w}, yw[4] = {y.x, y.y, y.z, y.w};
-#pragma unroll
-      for (int w = 0; w < 4; w++)
-#pragma unroll
-        for (int k = 0; k < 4; k++) {
-          const int t = (int)((xw[w] >> (8 * k)) & 0xFFu) - (int)((yw[w] >> (8 * k)) & 0xFFu);
-          s += (uint32_t)(t * t);
-        }
-    }
-    return canon0((float)s);
-  } else {
-    double s = 0.0;
-    for (int c = 0; c < nch; c++) {
-      const float4 x = *reinterpret_cast<const float4 *>(a + 16 * c);
-      const float4 y = *reinterpret_cast<const float4 *>(b + 16 * c);
-      const float xf[4] = {x.x, x.y, x.z, x.w}, yf[4] = {y.x, y.y, y.z, y.w};
-#pragma unroll
-      for (int k = 0; k < 4; k++) {
-        if (KIND == kF32L2) {
-          const double t = (double)xf[k] - (double)yf[k];
-          s = __builtin_fma(t, t, s);
-        } else {
-          s = __builtin_fma((double)xf[k], (double)yf[k], s);
-        }
-      }
-    }
-    return canon0(KIND == kF32IP ? (float)(-s) : (float)s);
-  }
-}
-
-__device__ __forceinline__ uint4 abs_4(uint4 v) {
-  return make_uint4(v.x & 0x7FFFFFFFu, v.y & 0x7FFFFFFFu, v.z & 0x7FFFFFFFu, v.w & 0x7FFFFFFFu);
-}
-
 __device__ __forceinline__ const uint8_t *row_of(const BuildArgs &a, uint32_t pos) {
   return a.pool.vecs + (size_t)a.ids[pos] * a.pool.stride;
 }
@@ -118,44 +76,11 @@ __global__ __launch_bounds__(64) void k_nnd_init(BuildArgs a) {
   if (u >= a.n) return;
   __shared__ uint32_t vL[128];
   __shared__ float dL[128];
-  const int ln = lane(), grp = ln >> 3, sub = ln & 7;
-  const int nch = a.pool.nch, K = (int)a.K;
+  const int ln = lane(), K = (int)a.K;
   const uint8_t *ru = row_of(a, u);
   for (int j = ln; j < 128; j += 64) vL[j] = j < K ? a.init[(size_t)u * K + j] : u;
   __syncthreads();
-  for (int j0 = 0; j0 < K; j0 += 16) {
-    const uint8_t *r0 = row_of(a, vL[j0 + grp]), *r1 = row_of(a, vL[j0 + 8 + grp]);
-    typename Acc<KIND>::T s0 = 0, s1 = 0;
-    double m0 = 0.0, m1 = 0.0;  // inner products: the terms' magnitudes
-    for (int c = sub; c < nch; c += 8) {
-      const uint4 q = ld16(ru + 16 * c), x0 = ld16(r0 + 16 * c), x1 = ld16(r1 + 16 * c);
-      if constexpr (KIND == kU8L2) {
-        const uint32_t qq = udot4(q.w, q.w, udot4(q.z, q.z, udot4(q.y, q.y, udot4(q.x, q.x, 0u))));
-        s0 = u8l2_4(q, x0, s0 + qq);
-        s1 = u8l2_4(q, x1, s1 + qq);
-      } else if constexpr (KIND == kF32L2) {
-        s0 = l2_4(q, x0, s0);
-        s1 = l2_4(q, x1, s1);
-      } else {
-        s0 = ip_4(q, x0, s0);
-        s1 = ip_4(q, x1, s1);
-        m0 = ip_4(abs_4(q), abs_4(x0), m0);
-        m1 = ip_4(abs_4(q), abs_4(x1), m1);
-      }
-    }
-    s0 = group_sum<8>(s0);
-    s1 = group_sum<8>(s1);
-    float d0 = finalize<KIND>(s0), d1 = finalize<KIND>(s1);
-    if constexpr (KIND != kU8L2) {
-      const double e0 = KIND == kF32IP ? group_sum<8>(m0) : s0, e1 = KIND == kF32IP ? group_sum<8>(m1) : s1;
-      if (!rounds_once(s0, e0 * 0x1p-42)) d0 = dist_seq<KIND>(ru, r0, nch);
-      if (!rounds_once(s1, e1 * 0x1p-42)) d1 = dist_seq<KIND>(ru, r1, nch);
-    }
-    if (sub == 0) {
-      dL[j0 + grp] = d0;
-      dL[j0 + 8 + grp] = d1;
-    }
-  }
+  row_dists<KIND>(ru, a.pool.nch, vL, dL, K, [&](uint32_t x) { return row_of(a, x); });
   __syncthreads();
   float d[2];
   uint32_t v[2];

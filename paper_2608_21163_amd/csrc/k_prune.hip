@@ -677,7 +677,11 @@ __global__ __launch_bounds__(64, 3) void k_rebuild_gram(RebuildArgs a) {
 }
 
 // Forward GrANDRobustPrune of new points with rows of any length: V_i with the
-// search's D, a 64-bit-key sort, then prune_gram.
+// search's D, a 64-bit-key sort, then prune_gram.  A search adds fp64 terms in
+// the order of its lane layout; the D that goes into the list and the records
+// is that of the sum in dimension order (row_dists), so that what a later
+// rebuild decides depends on the graph and the vectors alone, not on how an
+// entry came into its list or on an import between.
 template <int KIND, int NR>
 __global__ __launch_bounds__(64, 3) void k_fwd_prune_gram(FwdPruneArgs a) {
   __shared__ uint32_t spos[64 * (NR < 2 ? 2 : NR)];
@@ -711,6 +715,12 @@ __global__ __launch_bounds__(64, 3) void k_fwd_prune_gram(FwdPruneArgs a) {
   __syncthreads();
   uint32_t ntile = 0;
   const int nsel = prune_gram<KIND, NR>(P, p, m, R, a.coef, spos, dpos, oid, od, ntile);
+  if constexpr (KIND != kU8L2) {
+    if (nsel)
+      row_dists<KIND>(P.vecs + (size_t)p * P.stride, P.nch, oid, od, nsel,
+                      [&](uint32_t x) { return P.vecs + (size_t)x * P.stride; });
+    __syncthreads();
+  }
   if (ln < (int)R) {
     const bool in = ln < nsel;
     const uint32_t sid = in ? oid[ln] : kInvalid;

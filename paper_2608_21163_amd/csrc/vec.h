@@ -208,6 +208,103 @@ __device__ __forceinline__ float finalize(typename Acc<KIND>::T t) {
   return canon0((float)(-t));
 }
 
+// Dist of two rows of nch 16-byte chunks, one lane, dimensions in order
+// (zero padding adds nothing).
+template <int KIND>
+__device__ __forceinline__ float dist_seq(const uint8_t *a, const uint8_t *b, int nch) {
+  if (KIND == kU8L2) {
+    uint32_t s = 0;
+    for (int c = 0; c < nch; c++) {
+      const uint4 x = ld16(a + 16 * c), y = ld16(b + 16 * c);
+      const uint32_t xw[4] = {x.x, x.y, x.z, x.w}, yw[4] = {y.x, y.y, y.z, y.w};
+#pragma unroll
+      for (int w = 0; w < 4; w++)
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+          const int t = (int)((xw[w] >> (8 * k)) & 0xFFu) - (int)((yw[w] >> (8 * k)) & 0xFFu);
+          s += (uint32_t)(t * t);
+        }
+    }
+    return canon0((float)s);
+  } else {
+    double s = 0.0;
+    for (int c = 0; c < nch; c++) {
+      const float4 x = *reinterpret_cast<const float4 *>(a + 16 * c);
+      const float4 y = *reinterpret_cast<const float4 *>(b + 16 * c);
+      const float xf[4] = {x.x, x.y, x.z, x.w}, yf[4] = {y.x, y.y, y.z, y.w};
+#pragma unroll
+      for (int k = 0; k < 4; k++) {
+        if (KIND == kF32L2) {
+          const double t = (double)xf[k] - (double)yf[k];
+          s = __builtin_fma(t, t, s);
+        } else {
+          s = __builtin_fma((double)xf[k], (double)yf[k], s);
+        }
+      }
+    }
+    return canon0(KIND == kF32IP ? (float)(-s) : (float)s);
+  }
+}
+
+__device__ __forceinline__ uint4 abs_4(uint4 v) {
+  return make_uint4(v.x & 0x7FFFFFFFu, v.y & 0x7FFFFFFFu, v.z & 0x7FFFFFFFu, v.w & 0x7FFFFFFFu);
+}
+
+// The distances of the row `ru` to n >= 1 rows, row(ids[j]) (ids and out in
+// LDS), as the sums in dimension order round: 8 lanes a row, two rows of each
+// lane group and four chunks of a lane in flight; a sum whose order could move
+// the rounding is taken again, in order (about one in 130,000).
+template <int KIND, class Row>
+__device__ __forceinline__ void row_dists(const uint8_t *ru, int nch, const uint32_t *ids, float *out, int n, Row row) {
+  constexpr int U = 4;
+  const int grp = lane() >> 3, sub = lane() & 7;
+  for (int j0 = 0; j0 < n; j0 += 16) {
+    const uint8_t *r0 = row(ids[min(j0 + grp, n - 1)]), *r1 = row(ids[min(j0 + 8 + grp, n - 1)]);
+    typename Acc<KIND>::T s0 = 0, s1 = 0;
+    double m0 = 0.0, m1 = 0.0;  // inner products: the terms' magnitudes
+    for (int c0 = sub; c0 < nch + sub; c0 += 8 * U) {  // the same steps in every lane
+      uint4 q[U], x0[U], x1[U];
+#pragma unroll
+      for (int k = 0; k < U; k++) {
+        const size_t o = (size_t)min(c0 + 8 * k, nch - 1) * 16;
+        q[k] = ld16(ru + o);
+        x0[k] = ld16(r0 + o);
+        x1[k] = ld16(r1 + o);
+      }
+#pragma unroll
+      for (int k = 0; k < U; k++) {
+        if (c0 + 8 * k >= nch) q[k] = x0[k] = x1[k] = make_uint4(0, 0, 0, 0);
+        if constexpr (KIND == kU8L2) {
+          const uint32_t qq =
+              udot4(q[k].w, q[k].w, udot4(q[k].z, q[k].z, udot4(q[k].y, q[k].y, udot4(q[k].x, q[k].x, 0u))));
+          s0 = u8l2_4(q[k], x0[k], s0 + qq);
+          s1 = u8l2_4(q[k], x1[k], s1 + qq);
+        } else if constexpr (KIND == kF32L2) {
+          s0 = l2_4(q[k], x0[k], s0);
+          s1 = l2_4(q[k], x1[k], s1);
+        } else {
+          s0 = ip_4(q[k], x0[k], s0);
+          s1 = ip_4(q[k], x1[k], s1);
+          m0 = ip_4(abs_4(q[k]), abs_4(x0[k]), m0);
+          m1 = ip_4(abs_4(q[k]), abs_4(x1[k]), m1);
+        }
+      }
+    }
+    s0 = group_sum<8>(s0);
+    s1 = group_sum<8>(s1);
+    float d0 = finalize<KIND>(s0), d1 = finalize<KIND>(s1);
+    if constexpr (KIND != kU8L2) {
+      const double e0 = KIND == kF32IP ? group_sum<8>(m0) : s0, e1 = KIND == kF32IP ? group_sum<8>(m1) : s1;
+      if (!rounds_once(s0, e0 * 0x1p-42)) d0 = dist_seq<KIND>(ru, r0, nch);
+      if (!rounds_once(s1, e1 * 0x1p-42)) d1 = dist_seq<KIND>(ru, r1, nch);
+    }
+    if (sub == 0) {
+      if (j0 + grp < n) out[j0 + grp] = d0;
+      if (j0 + 8 + grp < n) out[j0 + 8 + grp] = d1;
+    }
+  }
+}
+
 // Distances from the slice to rows ids[0..cnt) (ids in LDS), written to
 // out[0..cnt) (LDS).  All gathers of RIF steps are issued before any is
 // consumed so that many rows are in flight per wave: 8 chunks per lane for
