@@ -203,7 +203,7 @@ template <> struct Gram<kF32L2> {
     return mfma_split(a.hi, a.lo, b.hi, b.lo, c);
   }
 };
-template <> struct Gram<kU8L2> {  // pool rows are whole 64-byte steps
+template <> struct Gram<kU8L2> {  // Vamana pool rows are whole 64-byte steps
   typedef v4i Acc;
   struct Raw { uint4 v; };
   typedef v4i Op;

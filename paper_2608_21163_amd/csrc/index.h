@@ -77,7 +77,7 @@ struct PoolView {
   uint8_t *active;
   float *adjd;     // Dist(u, N_out(u)[s]) beside every list entry of a Vamana pool (CAGRA: null);
                    // fp32: the sum in dimension order, whichever kernel wrote it
-  size_t stride;   // bytes per pool row (a multiple of 16; of 64 for uint8 rows)
+  size_t stride;   // bytes per pool row (a multiple of 16; of 64 for uint8 rows of a Vamana pool)
   int nch;         // 16-byte chunks per row
   uint32_t R;
   uint32_t cap;

@@ -253,11 +253,15 @@ template <> struct Join<kU8L2> {
   typedef v4i Acc;
   typedef int Sq;
   typedef v4i Op;
-  static __device__ __forceinline__ int steps(int nch) { return nch >> 2; }
-  static __device__ __forceinline__ uint4 load(const uint8_t *row, int k, int g, int) {
-    return ld16(row + (size_t)k * 64 + (size_t)g * 16);
+  static __device__ __forceinline__ int steps(int nch) { return (nch + 3) >> 2; }
+  static __device__ __forceinline__ uint4 load(const uint8_t *row, int k, int g, int nch) {
+    const int c = 4 * k + g;
+    return ld16(row + (size_t)(c < nch ? c : 0) * 16);
   }
-  static __device__ __forceinline__ Op op(uint4 v, uint4, int, int, int) { return to_i8x16(v); }
+  // chunks past the row are the same in every row, so they add nothing
+  static __device__ __forceinline__ Op op(uint4 v, uint4, int k, int g, int nch) {
+    return to_i8x16(4 * k + g < nch ? v : make_uint4(0, 0, 0, 0));
+  }
   static __device__ __forceinline__ Sq square(const Op &o, Sq s) { return sq_i8x16(o, s); }
   static __device__ __forceinline__ Acc mul(const Op &a, const Op &b, Acc c) { return mfma_i8(a, b, c); }
   static __device__ __forceinline__ int row(int g, int i) { return 4 * g + i; }
