@@ -129,6 +129,7 @@ grand_status fail(grand_index *h, grand_status code, const std::string &msg) {
 }
 
 grand_status fail_dev(grand_index *h, hipError_t e, const char *what) {
+  (void)hipGetLastError();  // the error stays with this handle
   h->poisoned = true;
   h->err = std::string("HIP error in ") + what + ": " + hipGetErrorString(e);
   return GRAND_E_DEVICE;
@@ -322,12 +323,24 @@ bool on_device(const void *p, int *dev = nullptr) {
   return a.type == hipMemoryTypeDevice;
 }
 
+// Whether the device allocation of p holds `bytes` from p on.
+bool holds(const void *p, size_t bytes) {
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  if (hipMemGetAddressRange(&base, &size, const_cast<void *>(p)) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return (uintptr_t)p + bytes <= (uintptr_t)base + size;
+}
+
 // The buffers a search works in.  Queries of this GPU's memory that need no
 // padding are read, and results there written, where they lie: a copy each way
 // is a launch of about 5 us and a gap after it, which a single query of 95 us
 // sees (the call 132 -> 123 us without its four).  Anything else -- host
 // memory, another GPU's, a misaligned pointer, a result that overlaps another
-// buffer of the call -- goes through the staging buffers.
+// buffer of the call, an allocation shorter than the call needs (the copy
+// refuses it) -- goes through the staging buffers.
 struct SearchBuffers {
   const uint8_t *q;
   uint32_t *ids;
@@ -336,18 +349,18 @@ struct SearchBuffers {
 };
 SearchBuffers search_buffers(int dev, const void *queries, size_t row_bytes, size_t q_stride, uint32_t nq, uint32_t k,
                              uint32_t *out_ids, float *out_dists, uint8_t *st_q, uint32_t *st_ids, float *st_d) {
-  auto here = [dev](const void *p, size_t align) {
+  auto here = [dev](const void *p, size_t bytes, size_t align) {
     int d = -1;
-    return (uintptr_t)p % align == 0 && on_device(p, &d) && d == dev;
+    return (uintptr_t)p % align == 0 && on_device(p, &d) && d == dev && holds(p, bytes);
   };
   auto apart = [](const void *a, size_t na, const void *b, size_t nb) {
     return (uintptr_t)a + na <= (uintptr_t)b || (uintptr_t)b + nb <= (uintptr_t)a;
   };
   const size_t qb = (size_t)nq * row_bytes, ob = (size_t)nq * k * 4;
   SearchBuffers s;
-  const bool out = here(out_ids, 4) && here(out_dists, 4) && apart(out_ids, ob, out_dists, ob) &&
+  const bool out = here(out_ids, ob, 4) && here(out_dists, ob, 4) && apart(out_ids, ob, out_dists, ob) &&
                    apart(out_ids, ob, queries, qb) && apart(out_dists, ob, queries, qb);
-  const bool q = q_stride == row_bytes && here(queries, 16);
+  const bool q = q_stride == row_bytes && here(queries, qb, 16);
   s.copy_q = !q;
   s.copy_out = !out;
   s.q = q ? static_cast<const uint8_t *>(queries) : st_q;
@@ -1331,7 +1344,10 @@ grand_status rfail(grand_reader *r, grand_status code, const std::string &msg) {
 #define RCHK(r, x)                                                                     \
   do {                                                                                 \
     hipError_t e_ = (x);                                                               \
-    if (e_ != hipSuccess) return rfail((r), GRAND_E_DEVICE, std::string(#x ": ") + hipGetErrorString(e_)); \
+    if (e_ != hipSuccess) {                                                            \
+      (void)hipGetLastError();                                                         \
+      return rfail((r), GRAND_E_DEVICE, std::string(#x ": ") + hipGetErrorString(e_)); \
+    }                                                                                  \
   } while (0)
 }  // namespace
 
