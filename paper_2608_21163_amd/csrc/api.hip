@@ -1081,8 +1081,10 @@ grand_status grand_build_cagra(grand_index *h, const void *vecs, const uint32_t 
   HCHK(h, launch_build_init(h->kind, a, h->stream));
   // nodes per range: what should fill nine tenths of the record buffers, by
   // the proposals per node of the range before (of the first one: every pair
-  // of 2 S new candidates, both ways)
-  double per_node = 2.0 * S * (2.0 * S - 1.0);
+  // of 2 S new candidates, both ways).  A range that made more than fit is
+  // launched again for its blocks that found no room, in ranges sized by what
+  // it made itself, so that no block is joined more than a few times.
+  double per_node = 2.0 * S * (2.0 * S - 1.0), again = 0.0;
   for (uint32_t it = 0; it < iters; it++) {
     // samples, recorded at their targets and grouped
     HCHK(h, launch_build_sample(a, h->stream));
@@ -1090,28 +1092,30 @@ grand_status grand_build_cagra(grand_index *h, const void *vecs, const uint32_t 
     HCHK(h, launch_build_cands(a, h->stream));
     HCHK(h, hipMemcpyAsync(a.nid, a.lid, nk * 4, hipMemcpyDeviceToDevice, h->stream));
     HCHK(h, hipMemcpyAsync(a.nd, a.ld, nk * 4, hipMemcpyDeviceToDevice, h->stream));
-    uint32_t v0 = 0;
+    uint32_t v0 = 0, redo = 0;  // nodes below redo: only blocks that found no room
     while (v0 < n) {
-      const double fit = 0.9 * (double)h->rcap / std::max(per_node, 1.0);
+      a.retry = v0 < redo;
+      const double fit = 0.9 * (double)h->rcap / std::max(a.retry ? again : per_node, 1.0);
       a.v0 = v0;
-      a.v1 = (uint32_t)std::min<double>(n, (double)v0 + std::max(fit, 1.0));
-      a.retry = 0;
-      for (;;) {  // the range, then its blocks that found no room
-        HCHK(h, launch_fill_u32(&h->ds->n_prop, 0u, 1, h->stream));
-        HCHK(h, launch_build_join(h->kind, a, h->stream));
-        HCHK(h, hipMemcpyAsync(&h->hs->n_prop, &h->ds->n_prop, sizeof(uint32_t), hipMemcpyDeviceToHost, h->stream));
-        HCHK(h, hipStreamSynchronize(h->stream));
-        const uint32_t np = h->hs->n_prop;
-        if (!a.retry) per_node = (double)np / (a.v1 - v0);
-        const size_t nrec = std::min<size_t>(np, h->rcap);
-        if (nrec) {
-          if ((s = run_group(h, nrec)) != GRAND_OK) return s;
-          HCHK(h, launch_build_merge(a, persistent_grid(n), h->stream));
-        }
-        if (np <= h->rcap) break;
-        a.retry = 1;
+      a.v1 = (uint32_t)std::min<double>(a.retry ? redo : n, (double)v0 + std::max(fit, 1.0));
+      HCHK(h, launch_fill_u32(&h->ds->n_prop, 0u, 1, h->stream));
+      HCHK(h, launch_build_join(h->kind, a, h->stream));
+      HCHK(h, hipMemcpyAsync(&h->hs->n_prop, &h->ds->n_prop, sizeof(uint32_t), hipMemcpyDeviceToHost, h->stream));
+      HCHK(h, hipStreamSynchronize(h->stream));
+      const uint32_t np = h->hs->n_prop;
+      const double made = (double)np / (a.v1 - v0);
+      if (!a.retry) per_node = made;
+      const size_t nrec = std::min<size_t>(np, h->rcap);
+      if (nrec) {
+        if ((s = run_group(h, nrec)) != GRAND_OK) return s;
+        HCHK(h, launch_build_merge(a, persistent_grid(n), h->stream));
       }
-      v0 = a.v1;
+      if (np > h->rcap) {
+        redo = a.retry ? redo : a.v1;
+        again = made;
+      } else {
+        v0 = a.v1;
+      }
     }
     std::swap(a.lid, a.nid);
     std::swap(a.ld, a.nd);
