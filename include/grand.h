@@ -143,8 +143,9 @@ grand_status grand_insert_batch(grand_index *h, const void *vecs, const uint32_t
  *   distinct positions in [0, n) other than p, the random initial neighbours
  *   (drawn by the caller, so that a run can be reproduced).
  * Requires R <= knn <= 128, knn < n, 1 <= sample <= 32, and
- * n * (12 sample^2 - 2 sample) < 2^32 (proposals of one round).  The medoid
- * is computed at the end.  Argument and validation errors change nothing.
+ * n * (12 sample^2 - 2 sample) < 2^32 (proposals of one round).  The call
+ * works in up to 640 MB of record buffers (and a few arrays of n lists), which
+ * it gives back when it ends.  The medoid is computed at the end.  Argument and validation errors change nothing.
  * Errors: GRAND_E_ARG
  * (wrong variant, index not empty, bad sizes or initial lists, non-finite
  * element), GRAND_E_ID, GRAND_E_CAPACITY, GRAND_E_OOM. */

@@ -272,14 +272,18 @@ grand_status ensure_batch(grand_index *h, uint32_t n) {
   return GRAND_OK;
 }
 
-grand_status ensure_records(grand_index *h, size_t n) {
-  if (n <= h->rcap) return GRAND_OK;
-  HCHK(h, hipStreamSynchronize(h->stream));
-  size_t nc = std::max<size_t>(n, h->rcap + h->rcap / 2);
+void free_records(grand_index *h) {
   dfree(h->rec_t); dfree(h->rec_s); dfree(h->rec_d); dfree(h->gsrc); dfree(h->gd);
   dfree(h->grp.pt); dfree(h->grp.ps); dfree(h->grp.pd); dfree(h->grp.mat); dfree(h->grp.mato); dfree(h->grp.tmp);
   h->rcap = 0;
   h->grp.rcap = 0;
+}
+
+grand_status ensure_records(grand_index *h, size_t n) {
+  if (n <= h->rcap) return GRAND_OK;
+  HCHK(h, hipStreamSynchronize(h->stream));
+  size_t nc = std::max<size_t>(n, h->rcap + h->rcap / 2);
+  free_records(h);
   const bool two = group_two_level(h->p.capacity);
   const size_t mw = two ? group_mat_words(h->p.capacity, nc) : 0;
   if (dalloc(&h->rec_t, nc) || dalloc(&h->rec_s, nc) || dalloc(&h->rec_d, nc) || dalloc(&h->gsrc, nc) ||
@@ -293,6 +297,19 @@ grand_status ensure_records(grand_index *h, size_t n) {
   if (two) h->grp.rcap = nc;
   return GRAND_OK;
 }
+
+// Gives the record buffers' growth during a call back when it ends.
+struct RecordsBack {
+  grand_index *h;
+  size_t was;
+  ~RecordsBack() {
+    if (h->poisoned || h->rcap <= was || hipStreamSynchronize(h->stream) != hipSuccess) return;
+    free_records(h);
+    const std::string err = h->err;
+    (void)ensure_records(h, was);  // without memory the next call that needs them asks again
+    h->err = err;
+  }
+};
 
 grand_status ensure_query(grand_index *h, uint32_t nq, uint32_t k) {
   if (nq <= h->qcap && k <= h->qk) return GRAND_OK;
@@ -1017,11 +1034,12 @@ grand_status grand_build_cagra(grand_index *h, const void *vecs, const uint32_t 
     (void)hipGetLastError();
     return fail(h, GRAND_E_OOM, "device allocation of the construction buffers failed");
   }
-  // the record buffers the index holds for its batches, grown to the sample
-  // and reverse-edge records if needed; the proposals of a round are written
+  // the record buffers the index holds for its batches, grown for the call to
+  // the sample and reverse-edge records; the proposals of a round are written
   // and merged in ranges of nodes that fill them.  Up to 20M records (640 MB):
   // a construction of 100,000 x 100 makes 380M proposals in six rounds, in 21
   // ranges instead of 61 with the 6.4M its edges need (55 ms against 62).
+  const RecordsBack back{h, h->rcap};
   const size_t need = std::max<size_t>(std::max<size_t>((size_t)n * 2 * S, (size_t)n * R), max_prop);
   const size_t want = std::max<size_t>(need, std::min<size_t>((size_t)n * max_prop, (size_t)20 << 20));
   if (ensure_records(h, want) != GRAND_OK) {
