@@ -20,8 +20,8 @@ CASES = {
     "f32_l2_d24": ("f32", "l2", 24, 2500, 40, 20, 10, 3),
     "u8_l2_d128": ("u8", "l2", 128, 3000, 32, 16, 8, 4),
     "u8_l2_d64_r30": ("u8", "l2", 64, 2000, 48, 30, 12, 2),
-    # large samples: a round's proposals (tens of millions) exceed the record
-    # buffers (n * 2 * sample), so the joins are written and merged in chunks
+    # large samples: a round's proposals (26.7M) exceed the record buffers (20M),
+    # so the joins are written and merged in ranges of nodes
     "f32_l2_d16_chunked": ("f32", "l2", 16, 8000, 64, 32, 32, 2),
 }
 

@@ -22,7 +22,7 @@ def test_host_and_device_rows_agree(dtype, metric, dim):
     import torch
 
     from paper_2608_21163_amd import GrandIndex
-    from paper_2608_21163_amd.grand import Reader
+    from paper_2608_21163_amd.grand import STATIC_SCRATCH_BYTES, Reader
 
     say(f"[host rows] {dtype} {metric} d{dim}")
     n, nq = 900, 77
@@ -40,10 +40,15 @@ def test_host_and_device_rows_agree(dtype, metric, dim):
         g.import_graph(put(x), st["adj"], st["deg"], st["active"], st["medoid"])
         r = Reader(g)
         out = [st["adj"], *g.search(put(q), 10, 32), *g.search_static(put(q), 10, 32), *r.search(put(q), 10, 32)]
-        # results that leave no room to stage the packed rows beside them
-        big = np.tile(q, (4096 * 256 // (nq * 10), 1))[:6_500]
-        if 6_500 * ((dim * x.itemsize + 4 * (metric == "mips") + 15) // 16 * 16) + 2 * 6_500 * 128 <= 8 << 20:
-            out += list(g.search_static(put(big), 32, 32))
+        row, stride = dim * x.itemsize, (dim * x.itemsize + 4 * (metric == "mips") + 15) // 16 * 16
+        if stride != row:
+            # as many results as fit, which leaves no room to stage the packed rows beside them
+            m = (STATIC_SCRATCH_BYTES - 3 * 256) // (stride + 2 * 256 * 4)
+            used = (m * stride + 255) // 256 * 256 + 2 * (m * 256 * 4)
+            assert used <= STATIC_SCRATCH_BYTES < used + m * row
+            big = np.tile(q, (m // nq + 1, 1))[:m]
+            out += list(g.search_static(put(big), 256, 256))
+            assert all(np.array_equal(a, b) for a, b in zip(out[-2:], g.search(put(big), 256, 256)))
         got.append([np.array(a) for a in out])
         r.close()
         g.close()
