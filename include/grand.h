@@ -270,9 +270,10 @@ typedef struct {
   uint64_t inserted, deleted, queried;
   uint64_t search_hops[3];         /* [insert, delete, query] searches: nodes expanded */
   uint64_t search_evals[3];        /* distance evaluations (row gathers) of those searches */
-  uint64_t fwd_evals;              /* pairwise distance evaluations in forward prunes */
+  uint64_t fwd_evals;              /* pairwise distance evaluations in forward prunes (a matrix-core
+                                      tile counts its 16 x 16) */
   uint64_t fwd_prunes;             /* forward GrANDRobustPrune invocations */
-  uint64_t rebuild_evals;          /* distance evaluations in dirty rebuilds (D_u and pairwise) */
+  uint64_t rebuild_evals;          /* pairwise distance evaluations in dirty rebuilds, likewise */
   uint64_t rebuild_prunes;         /* dirty rebuilds that ran GrANDRobustPrune */
   uint64_t dirty;                  /* dirty nodes rebuilt (or CAGRA targets / affected nodes) */
   uint64_t rebuild_records;        /* scratch records read by dirty rebuilds */

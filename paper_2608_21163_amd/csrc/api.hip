@@ -1038,7 +1038,9 @@ grand_status grand_build_cagra(grand_index *h, const void *vecs, const uint32_t 
   // the sample and reverse-edge records; the proposals of a round are written
   // and merged in ranges of nodes that fill them.  Up to 20M records (640 MB):
   // a construction of 100,000 x 100 makes 380M proposals in six rounds, in 21
-  // ranges instead of 61 with the 6.4M its edges need (55 ms against 62).
+  // ranges (45.0 ms; 46.6 with 10M records, 47.7 with 6.4M, which its edges
+  // need, 44.5 with 40M), of 30,000 15.3 ms (15.9 with 5M, 15.2 with 40M), of
+  // 300,000 127 ms (128 with the 19.2M of its edges, 121 with 40M).
   const RecordsBack back{h, h->rcap};
   const size_t need = std::max<size_t>(std::max<size_t>((size_t)n * 2 * S, (size_t)n * R), max_prop);
   const size_t want = std::max<size_t>(need, std::min<size_t>((size_t)n * max_prop, (size_t)20 << 20));

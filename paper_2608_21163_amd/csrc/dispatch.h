@@ -9,7 +9,9 @@
 //   class E: rows of <= 256 chunks         -> 64 lanes per row, <= 4 chunks per lane
 // Four chunks a lane keep the query in 16 registers: with 16 lanes and 16
 // chunks for every row above class B a search held 296 registers, one wave per
-// SIMD (2,000 searches of 100K x 960 fp32 2.09 ms; now 1.55).
+// SIMD (2,000 searches of 100K x 960 fp32 2.09 ms; now 1.55).  Few searches
+// gain as well below class E: one, and 1,000, of 50K x 300 0.91 -> 0.49 and 1.23
+// -> 0.71 ms, of 50K x 512 1.04 -> 0.52 and 1.35 -> 1.06.
 #pragma once
 #include "index.h"
 #include "vec.h"

@@ -27,7 +27,7 @@
 //
 // Measured, fp32, against one lane per candidate summing fp64 (whose
 // arithmetic was the bound): rebuilds of a 10,000-point batch on 1M x 96 6.93
-// -> 0.88 ms per launch, forward prunes 0.99 -> 0.21 ms; with 2,000-point
+// -> 0.88 ms per launch, forward prunes 0.99 -> 0.22 ms; with 2,000-point
 // batches on 100K x 960 4.67 -> 0.35 ms and 3.50 -> 0.40 ms.  What bounds it
 // now is the issue of the splits and products and the selection around them,
 // at three waves per SIMD (the accumulators take 60 registers; four waves

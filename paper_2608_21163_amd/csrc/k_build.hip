@@ -67,9 +67,8 @@ __global__ __launch_bounds__(64) void k_nnd_check(BuildArgs a) {
 }
 
 // Lists from the initial positions, ascending by (Dist, position), all new.
-// The rows are gathered 8 lanes a row, two rows of each lane group in flight
-// (one lane a row, 16 bytes at a time, took 4.2 ms for 100,000 x 128 rows of
-// 400 bytes; this takes 0.9).
+// The rows are gathered by row_dists (one lane a row, 16 bytes at a time, took
+// 4.2 ms for 100,000 x 128 rows of 400 bytes; this takes 0.86).
 template <int KIND>
 __global__ __launch_bounds__(64) void k_nnd_init(BuildArgs a) {
   const uint32_t u = blockIdx.x;
@@ -291,8 +290,10 @@ __device__ __forceinline__ double join_sum(double v) {
 // from rows in LDS, counted in one pass and written in a second, took 10 ms a
 // round (100,000 x 100 fp32, S = 16; 6 waves per CU for the LDS, three fp64
 // instructions per dimension of a pair).  With every row converted once per
-// tile product it takes 2.2 ms a round, which are the rows' latency at two to
-// three waves per SIMD (176 registers) and the 63M records written.
+// tile product it takes 2.2 ms a round, at two to three waves per SIMD (176
+// registers).  Its 63M records would be written in 0.2 ms at the rate of a large
+// copy; the cursor weighs more: a second returning atomic of every block on its
+// address took 7 ms a round.
 template <int KIND, int NT>
 __global__ __launch_bounds__(64, NT == 4 ? 3 : 1) void k_nnd_join(BuildArgs a) {
   typedef Join<KIND> J;

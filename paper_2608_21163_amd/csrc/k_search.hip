@@ -341,8 +341,17 @@ hipError_t launch_search(int kind, int vc, const SearchArgs &a, hipStream_t st) 
   if (a.nq == 0) return hipSuccess;
   // The longest rows, where a launch leaves a SIMD to every search: registers
   // don't limit the waves then, and 16 lanes a row need the fewest instructions
-  // for its sums (1,000 searches of beam 256 on 100K x 769: 1.42 ms, 64 lanes
-  // 1.65; 2,000 of beam 128 on 100K x 960: 2.09 and 1.55).
+  // for its sums.  With more searches than SIMDs the second wave per SIMD of
+  // the 64-lane form counts for more.  16 and 64 lanes, ms a launch:
+  //   1,000 searches, beam 256, 100K x 769                     1.42   1.65
+  //   2,000, beam 128, 100K x 960 of a built graph             2.09   1.55
+  //   1,024 and 1,025, beam 128, 50K x 520 of a random graph   2.24   2.61,  3.87   2.62
+  //   1,024 and 1,025, 50K x 700                               2.72   3.00,  4.38   3.01
+  //   1,024 and 1,025, 50K x 960                               3.56   3.83,  5.17   3.82
+  // At a few hundred searches or one, where the chain of a hop is all that
+  // counts, 64 lanes are the faster form (one search: 1.80 and 1.70 at 520, 2.17
+  // and 1.77 at 960; 500: 2.44 and 1.99 at 960): the line could have a lower
+  // end, between 500 and 1,000 searches.
   static const uint32_t alone = simds();
   if (vc == kVcE && a.nq <= alone) {
     GR_DISPATCH_ALONE(kind, GR_DISPATCH_N(a.ell, { return (launch_search_t<KIND, LPV, CPL, NR>(a, st)); }));
