@@ -103,6 +103,7 @@ struct grand_index {
   uint32_t *rec_t = nullptr, *rec_s = nullptr, *gsrc = nullptr;
   float *rec_d = nullptr, *gd = nullptr;
   RowStage rows;  // packed rows from host memory on their way into padded ones
+  bool imported = false;  // list distances may be unknown (kUnknownDist)
   // query buffers
   uint32_t qcap = 0, qk = 0;
   uint8_t *q_vecs = nullptr;
@@ -467,6 +468,7 @@ grand_status run_rebuild(grand_index *h, size_t nrec, const uint8_t *in_batch) {
   a.gsrc = h->gsrc;
   a.gd = h->gd;
   a.in_batch = in_batch;
+  a.fill = h->imported;
   a.P = h->p.P;
   a.coef = h->coef;
   a.ds = h->ds;
@@ -1554,7 +1556,10 @@ grand_status grand_import_graph(grand_index *h, const void *vecs, const uint32_t
   HCHK(h, hipMemcpyAsync(h->pool.active, active, cap, hipMemcpyDefault, h->stream));
   if ((s = clear_errors(h)) != GRAND_OK) return s;
   if (h->mips) HCHK(h, launch_mips_augment(h->pool.vecs, cap, h->stride, h->p.dim, h->p.mips_norm, h->ds, h->stream));
-  HCHK(h, launch_adj_dists(h->pool, h->kind, h->stream));
+  if (h->pool.adjd) {
+    HCHK(h, launch_fill_u32(reinterpret_cast<uint32_t *>(h->pool.adjd), kUnknownDist, cap * h->p.R, h->stream));
+    h->imported = true;
+  }
   HCHK(h, hipMemsetAsync(&h->ds->n_count, 0, sizeof(unsigned long long), h->stream));
   hipLaunchKernelGGL(k_import_check, dim3(4096), dim3(256), 0, h->stream, h->pool, h->ds);
   hipLaunchKernelGGL(k_count_active, dim3(1024), dim3(256), 0, h->stream, h->pool.active, h->p.capacity, h->ds);

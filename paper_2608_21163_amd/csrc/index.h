@@ -69,6 +69,8 @@ enum { kErrRange = 1, kErrRepeat = 2, kErrState = 3, kErrNonFinite = 4, kErrNorm
 // (CPL) of the distance machinery, chosen from the padded row length.
 enum { kVcA = 0, kVcB, kVcC, kVcD, kVcE };  // <= 8, 32, 64, 128 and 256 chunks
 
+constexpr uint32_t kUnknownDist = 0x7FFFFFFFu;  // a NaN that no kernel computes
+
 // Pool view passed to kernels.
 struct PoolView {
   uint8_t *vecs;
@@ -76,7 +78,8 @@ struct PoolView {
   uint32_t *deg;
   uint8_t *active;
   float *adjd;     // Dist(u, N_out(u)[s]) beside every list entry of a Vamana pool (CAGRA: null);
-                   // fp32: the sum in dimension order, whichever kernel wrote it
+                   // fp32: the sum in dimension order, whichever kernel wrote it;
+                   // kUnknownDist after an import, until u is pruned
   size_t stride;   // bytes per pool row (a multiple of 16; of 64 for uint8 rows of a Vamana pool)
   int nch;         // 16-byte chunks per row
   uint32_t R;
@@ -149,6 +152,7 @@ struct RebuildArgs {
   uint32_t flag_cap;          // entries of qflag (bounds the list length)
   uint32_t *scan_tmp;         // compaction scratch (scan_tmp_words(flag_cap))
   int count_nodes;            // this launch counts dirty nodes and records read
+  int fill;                   // lists may hold unknown distances
   const uint32_t *goff;       // group offsets by target id (cap + 1)
   const uint32_t *gsrc;
   const float *gd;
@@ -261,8 +265,6 @@ hipError_t launch_mips_augment(uint8_t *rows, size_t n, size_t stride, uint32_t 
                                hipStream_t s);
 hipError_t launch_check_finite(const uint8_t *rows, uint32_t n, size_t stride, uint32_t dim, DevScalars *ds,
                                hipStream_t s);
-// Dist(u, v) for every entry of every list (after a bulk import).
-hipError_t launch_adj_dists(PoolView p, int kind, hipStream_t s);
 hipError_t launch_stage(PoolView p, const uint8_t *rows, const uint32_t *ids, uint32_t n, uint32_t *bidx,
                         hipStream_t s);
 hipError_t launch_mark_batch(const uint32_t *ids, uint32_t n, uint8_t *in_batch, uint32_t *bidx, uint8_t v,

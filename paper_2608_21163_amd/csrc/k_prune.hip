@@ -751,45 +751,31 @@ hipError_t launch_fwd_prune(int kind, uint32_t max_iters, const FwdPruneArgs &a,
   return hipErrorInvalidValue;
 }
 
-// One wave per row, lane s for list entry s: the squared distance of u and
-// its s-th neighbour (0 for an empty slot), exact for uint8 rows, summed in
-// fp64 in dimension order and rounded once for fp32 rows.
+// The list distances that an import left unknown, of the nodes that are about
+// to be pruned: one wave per node.  (Computing every list's at the import took
+// a gather of the whole graph: 0.6 -> 6.9 ms for 50,000 x 960 fp32 rows of
+// device memory, 0.9 -> 1.7 for 100,000 x 200 bytes.)
 template <int KIND>
-__global__ void k_adj_dists(PoolView P) {
-  const int ln = threadIdx.x & 63;
-  const uint32_t w0 = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
-  for (uint32_t u = w0; u < P.cap; u += nw) {
-    if (ln >= (int)P.R) continue;
-    const uint32_t v = P.adj[(size_t)u * P.R + ln];
-    float d = 0.0f;
-    if (kvalid(v) && v < P.cap) {
-      const uint4 *x = reinterpret_cast<const uint4 *>(P.vecs + (size_t)u * P.stride);
-      const uint4 *y = reinterpret_cast<const uint4 *>(P.vecs + (size_t)v * P.stride);
-      typename Acc<KIND>::T acc = 0;
-      for (int c = 0; c < P.nch; c++) {
-        const uint4 a = x[c], b = y[c];
-        if constexpr (KIND == kU8L2) {
-          acc = udot4(a.x, a.x, acc);
-          acc = udot4(a.y, a.y, acc);
-          acc = udot4(a.z, a.z, acc);
-          acc = udot4(a.w, a.w, acc);
-          acc = u8l2_4(a, b, acc);  // + |b|^2 - 2 a.b
-        } else {
-          acc = l2_4(a, b, acc);
-        }
-      }
-      d = finalize<KIND>(acc);
-    }
-    P.adjd[(size_t)u * P.R + ln] = d;
+__global__ __launch_bounds__(64) void k_fill_dists(PoolView P, const uint32_t *list, const uint32_t *list_n) {
+  __shared__ uint32_t ids[64];
+  __shared__ float d[64];
+  const int ln = lane();
+  const uint32_t n = *list_n;
+  for (uint32_t it = blockIdx.x; it < n; it += gridDim.x) {
+    const uint32_t u = list[it];
+    const size_t at = (size_t)u * P.R + ln;
+    const uint32_t v = ln < (int)P.R ? P.adj[at] : kInvalid;
+    const bool open = kvalid(v) && __float_as_uint(P.adjd[at]) == kUnknownDist;
+    const uint64_t m = ballot(open);
+    if (!m) continue;
+    if (open) ids[mbcnt(m)] = v;
+    __syncthreads();
+    row_dists<KIND>(P.vecs + (size_t)u * P.stride, P.nch, ids, d, popc(m),
+                    [&](uint32_t x) { return P.vecs + (size_t)x * P.stride; });
+    __syncthreads();
+    if (open) P.adjd[at] = d[mbcnt(m)];
+    __syncthreads();
   }
-}
-hipError_t launch_adj_dists(PoolView p, int kind, hipStream_t s) {
-  if (!p.adjd || p.cap == 0) return hipSuccess;
-  size_t g = ((size_t)p.cap * 64 + 255) / 256;
-  if (g > 16384) g = 16384;
-  if (kind == kU8L2) hipLaunchKernelGGL(k_adj_dists<kU8L2>, dim3((uint32_t)g), dim3(256), 0, s, p);
-  else hipLaunchKernelGGL(k_adj_dists<kF32L2>, dim3((uint32_t)g), dim3(256), 0, s, p);
-  return hipGetLastError();
 }
 
 // One persistent rebuild kernel over the queue: twice the resident
@@ -819,6 +805,10 @@ hipError_t launch_rebuild(int kind, uint32_t R, uint32_t P, const RebuildArgs &a
     a.list = a0.queue;
     a.list_n = a0.queue_n;
     a.count_nodes = 0;
+  }
+  if (a.fill) {
+    if (kind == kU8L2) hipLaunchKernelGGL(k_fill_dists<kU8L2>, dim3(grid), dim3(64), 0, st, a.pool, a.list, a.list_n);
+    else hipLaunchKernelGGL(k_fill_dists<kF32L2>, dim3(grid), dim3(64), 0, st, a.pool, a.list, a.list_n);
   }
   // uint8 rows of 64 and 128 bytes: a node's tiles stay in registers and only
   // the tiles that still hold a live candidate are multiplied (0.42 ms per

@@ -9,9 +9,9 @@ selected i kills j in u's rebuild only by the second value."""
 import numpy as np
 import pytest
 
-from helpers import INVALID, canonical_rows, rows_to_adj
+from helpers import INVALID, canonical_rows, check_graph_invariants, rows_to_adj
 from oracle.oracle import Oracle
-from parity import say
+from parity import compare_states, say
 from workloads import IndexConfig
 
 pytestmark = pytest.mark.gpu
@@ -99,4 +99,33 @@ def test_records_of_a_delete(d, c):
     for s in (o, g):
         s.delete(np.array([P], np.uint32))
     _same(o, g, {I, J, M})
+    g.close()
+
+
+@pytest.mark.parametrize("dtype,d,R,P", [("f32", 20, 24, 64), ("f32", 300, 16, 100), ("f32", 7, 15, 64),
+                                         ("u8", 128, 24, 64), ("u8", 40, 18, 64), ("u8", 200, 64, 128)])
+def test_updates_after_an_import(dtype, d, R, P):
+    """An import leaves the list distances to the first rebuild that prunes a
+    node; lists grow, shrink and are pruned with some of them known."""
+    from paper_2608_21163_amd import GrandIndex
+
+    say(f"[list distances] updates after an import, {dtype} d{d} R{R} P{P}")
+    n, b = 1_200, 100
+    cfg = IndexConfig("vamana", dtype, "l2", d, n, R, 48, P=P)
+    g0 = np.random.default_rng(51)
+    x = g0.integers(0, 256, (n, d)).astype(np.uint8) if dtype == "u8" else g0.standard_normal((n, d)).astype(np.float32)
+    ids = g0.permutation(n).astype(np.uint32)
+    o, g = Oracle(cfg), GrandIndex.from_config(cfg, max_batch=400)
+    for s in range(0, 800, 400):
+        assert o.insert(ids[s:s + 400], x[ids[s:s + 400]]) == 0
+    st = o.export()
+    g.import_graph(x, st["adj"], st["deg"], st["active"], st["medoid"])
+    for k in range(4):
+        new, old = ids[800 + k * b:800 + (k + 1) * b], ids[k * b:(k + 1) * b]
+        for s in (o, g):
+            s.insert(new, x[new])
+            s.delete(old)
+        gst = g.export()
+        check_graph_invariants(gst, R)
+        assert compare_states(gst, o.export(), "vamana") == 0
     g.close()
