@@ -101,7 +101,9 @@ __device__ __forceinline__ void closest_c(const RepairArgs &a, uint32_t cv, uint
   Slice<KIND, LPV, CPL> s;
   load_slice<KIND, LPV, CPL>(s, P.vecs + (size_t)x * P.stride, P.nch);
   __syncthreads();
-  wave_dists<KIND, LPV, CPL>(s, P.vecs, P.stride, P.nch, lst, ldist, cnt);
+  // a record's distance is that of the sum in dimension order
+  wave_dists<KIND, LPV, CPL, KIND == kF32L2>(s, P.vecs, P.stride, P.nch, lst, ldist, cnt,
+                                             P.vecs + (size_t)x * P.stride);
   __syncthreads();
   evals += (unsigned long long)cnt;
   float d[1] = {ln < cnt ? ldist[ln] : finf()};
@@ -110,17 +112,6 @@ __device__ __forceinline__ void closest_c(const RepairArgs &a, uint32_t cv, uint
   wave_sort<1>(d, id);
   od = d[0];
   oi = id[0];
-  if constexpr (KIND != kU8L2) {  // a record's distance is that of the sum in dimension order
-    const int n = min((int)a.c, cnt);
-    lst[ln] = oi;
-    __syncthreads();
-    if (n)
-      row_dists<KIND>(P.vecs + (size_t)x * P.stride, P.nch, lst, ldist, n,
-                      [&](uint32_t y) { return P.vecs + (size_t)y * P.stride; });
-    __syncthreads();
-    if (ln < n) od = ldist[ln];
-    __syncthreads();
-  }
 }
 
 // One wavefront per deleted node, any element type: each neighbour's c

@@ -310,10 +310,20 @@ __device__ __forceinline__ void row_dists(const uint8_t *ru, int nch, const uint
 // consumed so that many rows are in flight per wave: 8 chunks per lane for
 // rows of 8 lanes (64 rows of one chunk a lane, 16 rows of four), 32 for
 // longer rows, whose few sums are folded (fold_sum), and one row's 16 chunks
-// per lane for the longest rows of a wave that has its SIMD to itself.
-template <int KIND, int LPV, int CPL>
+// per lane for the longest rows of a wave that has its SIMD to itself.  ORDER
+// (squared L2; qrow: the slice's row): the distances are those of the sums in
+// dimension order, a sum whose order could move its rounding taken again.
+template <int KIND, int LPV, int CPL, bool ORDER = false>
 __device__ __forceinline__ void wave_dists(const Slice<KIND, LPV, CPL>& s, const uint8_t* __restrict__ vecs,
-                                           size_t stride, int nch, const uint32_t* ids, float* out, int cnt) {
+                                           size_t stride, int nch, const uint32_t* ids, float* out, int cnt,
+                                           const uint8_t* qrow = nullptr) {
+  static_assert(!ORDER || KIND != kF32IP, "inner products need the magnitude of their terms");
+  auto dist = [&](typename Acc<KIND>::T t, int c) {
+    if constexpr (ORDER && KIND == kF32L2) {
+      if (!rounds_once(t, t * 0x1p-42)) return dist_seq<KIND>(qrow, vecs + (size_t)ids[c] * stride, nch);
+    }
+    return finalize<KIND>(t);
+  };
   constexpr int G = 64 / LPV;
   constexpr bool kFold = LPV >= 16 && CPL <= 4;
   constexpr int RIF = kFold ? 32 / CPL : CPL >= 8 ? 1 : 8 / CPL;
@@ -363,7 +373,7 @@ __device__ __forceinline__ void wave_dists(const Slice<KIND, LPV, CPL>& s, const
       }
       const typename Acc<KIND>::T v = fold_sum<RIF, LPV>(t);
       const int c = base + fold_index<RIF, LPV>() * G + grp;
-      if (ln % (LPV / RIF) == 0 && c < cnt) out[c] = finalize<KIND>(v);
+      if (ln % (LPV / RIF) == 0 && c < cnt) out[c] = dist(v, c);
     } else {
 #pragma unroll
       for (int rr = 0; rr < RIF; rr++) {
@@ -381,7 +391,7 @@ __device__ __forceinline__ void wave_dists(const Slice<KIND, LPV, CPL>& s, const
         if (rr >= steps) break;
         const int c = base + rr * G + grp;
         typename Acc<KIND>::T t = group_sum<LPV>(partial<KIND, LPV, CPL>(s, b[rr]));
-        if (sub == 0 && c < cnt) out[c] = finalize<KIND>(t);
+        if (sub == 0 && c < cnt) out[c] = dist(t, c);
       }
     }
   }
