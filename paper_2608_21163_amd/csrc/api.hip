@@ -7,6 +7,7 @@
 
 #include <algorithm>
 #include <mutex>
+#include <optional>
 #include <string>
 #include <tuple>
 #include <vector>
@@ -299,16 +300,49 @@ grand_status ensure_records(grand_index *h, size_t n) {
   return GRAND_OK;
 }
 
-// Gives the record buffers' growth during a call back when it ends.
-struct RecordsBack {
+// Larger record buffers for one call: the index's own are put aside and come
+// back when it ends (they are freed for the call, and allocated again after it,
+// only where both do not fit).
+struct RecordsAside {
   grand_index *h;
   size_t was;
-  ~RecordsBack() {
-    if (h->poisoned || h->rcap <= was || hipStreamSynchronize(h->stream) != hipSuccess) return;
+  uint32_t *rec_t, *rec_s, *gsrc;
+  float *rec_d, *gd;
+  GroupBufs grp;
+  bool kept = true;
+  explicit RecordsAside(grand_index *h_)
+      : h(h_), was(h->rcap), rec_t(h->rec_t), rec_s(h->rec_s), gsrc(h->gsrc), rec_d(h->rec_d), gd(h->gd), grp(h->grp) {
+    forget();
+  }
+  void forget() {
+    h->rec_t = h->rec_s = h->gsrc = nullptr;
+    h->rec_d = h->gd = nullptr;
+    h->grp.pt = h->grp.ps = h->grp.mat = h->grp.mato = h->grp.tmp = nullptr;
+    h->grp.pd = nullptr;
+    h->rcap = h->grp.rcap = 0;
+  }
+  void put_back() {
+    h->rec_t = rec_t; h->rec_s = rec_s; h->gsrc = gsrc;
+    h->rec_d = rec_d; h->gd = gd;
+    h->grp = grp;
+    h->rcap = was;
+  }
+  void drop() {
     free_records(h);
-    const std::string err = h->err;
-    (void)ensure_records(h, was);  // without memory the next call that needs them asks again
-    h->err = err;
+    put_back();
+    free_records(h);
+    kept = false;
+  }
+  ~RecordsAside() {
+    if (!h->poisoned) (void)hipStreamSynchronize(h->stream);
+    free_records(h);
+    if (kept) {
+      put_back();
+    } else if (!h->poisoned) {
+      const std::string err = h->err;
+      (void)ensure_records(h, was);  // without memory the next call that needs them asks again
+      h->err = err;
+    }
   }
 };
 
@@ -1043,12 +1077,18 @@ grand_status grand_build_cagra(grand_index *h, const void *vecs, const uint32_t 
   // ranges (45.0 ms; 46.6 with 10M records, 47.7 with 6.4M, which its edges
   // need, 44.5 with 40M), of 30,000 15.3 ms (15.9 with 5M, 15.2 with 40M), of
   // 300,000 127 ms (128 with the 19.2M of its edges, 121 with 40M).
-  const RecordsBack back{h, h->rcap};
   const size_t need = std::max<size_t>(std::max<size_t>((size_t)n * 2 * S, (size_t)n * R), max_prop);
   const size_t want = std::max<size_t>(need, std::min<size_t>((size_t)n * max_prop, (size_t)20 << 20));
-  if (ensure_records(h, want) != GRAND_OK) {
-    if (h->poisoned) return GRAND_E_DEVICE;
-    if ((s = ensure_records(h, need)) != GRAND_OK) return s;
+  std::optional<RecordsAside> aside;
+  if (want > h->rcap) {
+    aside.emplace(h);
+    s = ensure_records(h, want);
+    if (s == GRAND_E_OOM) s = ensure_records(h, need);
+    if (s == GRAND_E_OOM) {
+      aside->drop();
+      s = ensure_records(h, need);
+    }
+    if (s != GRAND_OK) return s;
     h->err.clear();
   }
   BuildArgs a{};
